@@ -89,7 +89,7 @@ corr_status corr_debug_read_plan(const corr_pyramid* pyr, int32_t* counts, int32
 int corr_debug_set_level_split(int max_queries);
 /*
  * Test and measurement hook (process-wide): which kernel corr_sample_backward runs.  CORR_BACKWARD_ITEMS (the
- * default): the forward pass's work items, both gradients as fp32 matrix-core contractions over an item's
+ * default): the forward pass's work items, both gradients as matrix-core contractions over an item's
  * windows.  CORR_BACKWARD_QUERIES: one wave per query on the vector ALU with a float atomic per footprint
  * point and channel (the earlier form; kept as a cross-check and as the slower side of the comparison).
  * Both give the same gradients up to fp32 summation order.  Returns the previous setting.

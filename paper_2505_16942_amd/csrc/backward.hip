@@ -105,27 +105,55 @@ __global__ __launch_bounds__(64 * BQ) void bwd_query_kernel(BwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The item form: the same work items as the forward block kernel (a target cell and up to 128 of its queries,
-// one fixed window of level-l points per level), and both gradients as dense contractions on the matrix cores.
+// The item form: the same work items as the forward block kernel (a target cell and up to 128 of its queries, at every
+// level the window of points their footprints cover), and both gradients as dense contractions on the matrix cores.
 // For one item and level, with G[point][query] the footprint weights of every query scattered over the window
 // (zero outside the query's footprint) and 1/sqrt(D) folded in:
 //     d f1[query][:]       += sum over points  G[point][query] * f2_l[point][:]       (M = queries, K = points)
 //     d f2_l[point][:]     += sum over queries G[point][query] * f1[query][:]         (M = points,  K = queries)
-// fp32 throughout: v_mfma_f32_16x16x4_f32 takes one fp32 element of A and of B per lane, so G (in LDS, one
-// column per query) and the channels-last fp32 feature rows feed it without any transposition.  G is built
-// CH points at a time from the tap gradients (a footprint point collects up to four taps); d f1 stays in
-// accumulators over all levels and is stored once (a query belongs to one item); the window's d f2_l rows go
-// out through float atomics once per item and pass, instead of once per query and footprint point.
-// Eight waves, two per SIMD: a wave owns 32 channels of a 256-channel group (16 of a 128-channel group for
-// D <= 128); lane = (K index lane/16, M or N index lane%16).  Feature rows come through buffer resources: an offset past the end reads zero and an atomic
-// there is dropped, so rows outside the level and empty query slots need no branch inside the loops.
+// fp32 in, fp32 accumulation, at fp32's precision on v_mfma_f32_16x16x32_bf16: every operand is the sum of three bf16
+// values (hi + mid + lo hold all 24 bits of an fp32 significand), and of the nine partial products the six that reach
+// 2^-24 are accumulated (hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi).  Six products at 16 times the rate of
+// v_mfma_f32_16x16x4_f32, which this replaced; the error against fp64 is the same (rms 1.8e-7 of d f1's).
+// Queries are ranked by target column and points are numbered column by column, so a tile of 16 queries and a run of 32
+// points meet only if the tile's footprints reach those columns; the others are skipped (about half of them at level
+// 0, where a full item's window is 25 columns wide and a tile's footprints are 11 or 12).
+// G is built CH points at a time from the tap gradients (a footprint point collects up to four taps) in LDS, three bf16
+// planes [point][query], 32-byte blocks XOR-swizzled by the point.  The second contraction reads its fragments along the
+// queries as they lie, the first one through the transposing LDS read.  The feature rows are the B operands: lane =
+// (channel, 8 consecutive points or queries), loaded as fp32 in that layout and split in registers; f1's fragments stay in
+// registers for the whole item.  d f1 stays in accumulators over all levels and is stored once (a query belongs to one
+// item, so its bits are the same on every call); the window's d f2_l rows go out through float atomics once per item and
+// pass, instead of once per query and footprint point.
+// Measured, D = 256: the call takes 1.21 ms on a 270 x 480 map and 0.205 ms on two 46 x 62 ones, against 1.62 and 0.28 ms with fp32
+// instructions, every tile against every point, and one 64-byte row piece per atomic.  An item's 156 us on 270 x 480 are 55 and 56
+// in the two contractions (matrix pipes 40 of both together), 17 in the scatter (serial work per footprint column), 14 waiting
+// for tap gradients and 8 clearing G; 30 of the second contraction's are its atomics, which all execute beyond the L2.  Half
+// of the waves on each contraction at the same time, the window's rows warmed into the L2 during the scatter, and loads
+// two runs ahead (spills) were no faster.
+// Eight waves, two per SIMD: a wave owns 32 channels of a 256-channel group (16 of a 128-channel group for D <= 128).
+// Feature rows come through buffer resources: an offset past the end reads zero and an atomic there is dropped, so rows
+// outside the level and empty query slots need no branch inside the loops.
 constexpr int NTI = 512;
-constexpr int GST = CORR_GROUP + 4;         // floats between G rows (bank shift 4 per row: a 16-row x 4-query read is conflict-free)
 constexpr int CH = 144;                     // window points per pass: level 2's window in one pass, level 0's in three
-constexpr int MTC = CH / 16;
-constexpr int TAB_PAD = 16;                 // the operand loads run three k-steps ahead: the tables end in invalid entries
+constexpr int QT = CORR_GROUP / 16;         // 16-query tiles
+constexpr int G_PLANE = CORR_GROUP * 2;     // bytes of a point in one plane
+constexpr int G_ROW = 3 * G_PLANE;
 constexpr int MAXKK = MAXK * MAXK;
-constexpr int ITEM_LDS = CH * GST * 4 + (CH + TAB_PAD) * 4 + (CORR_GROUP + TAB_PAD) * 4 + CORR_GROUP * 8 + MAXKK * CORR_GROUP * 4;
+constexpr int TAB = CH + 16;                // the last run of 32 points ends past the pass: invalid entries
+// LDS layout (bytes)
+constexpr int I_G = 0;                                  // [CH][3][128] bf16
+constexpr int I_ROW = I_G + CH * G_ROW;                 // [TAB] byte offset of each point's feature row; BAD_OFF: outside the level
+constexpr int I_Q = I_ROW + TAB * 4;                    // [128] by rank: byte offset of the query's feature row; BAD_OFF: empty
+constexpr int I_CX = I_Q + CORR_GROUP * 4;              // [128] each by rank: coordinates, pixel * 4 (BAD_OFF: empty), target column inside the cell
+constexpr int I_CY = I_CX + CORR_GROUP * 4;
+constexpr int I_PIX = I_CY + CORR_GROUP * 4;
+constexpr int I_COL = I_PIX + CORR_GROUP * 4;
+constexpr int I_HIST = I_COL + CORR_GROUP * 4;          // [16] queries per column
+constexpr int I_NEXT = I_HIST + 16 * 4;                 // the workgroup's next queue position
+constexpr int I_TAPS = I_HIST + 32 * 4;                 // [K*K][128] tap gradients of the level in work, by rank
+constexpr int ITEM_LDS = I_TAPS + MAXKK * CORR_GROUP * 4;
+static_assert(ITEM_LDS <= 160 * 1024 && I_ROW % 16 == 0 && I_Q % 16 == 0, "LDS layout");
 constexpr unsigned BAD_OFF = 0x80000000u;   // beyond every buffer here (each is below 2 GiB)
 
 struct BwdItemArgs {
@@ -151,7 +179,16 @@ struct BwdItemArgs {
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+typedef __attribute__((address_space(3))) u32x4* lds_u32x4;
+typedef __attribute__((address_space(3))) __bf16* lds_bf16;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const float* base, size_t floats) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(unsigned)(floats * 4), 0x00020000);
 }
@@ -166,66 +203,38 @@ __device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t r, unsigned off
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
-// d f2_l rows of one pass = G x f1 for MT 16-point tiles (rows past the window are zero in G), then out through
-// atomics.  k-step ks takes queries 4*ks + lg.  Software pipeline, pinned by the scheduling barriers: the f1 values
-// of step ks + 3, the table entry of step ks + 4 and the G fragments of step ks + 1 are on their way while the
-// matrix cores work on step ks.
-template <int NMT, int MT, int NTW>
-__device__ __forceinline__ void rows_gradient(const float* G, const unsigned* rowoff, const unsigned* q_off,
-                                              __amdgpu_buffer_rsrc_t r_f1, __amdgpu_buffer_rsrc_t r_d2,
-                                              unsigned ch4, int lr, int lg) {
-    f32x4 acc2[MT][NTW];
+// three bf16 values whose sum is the fp32 value: rounded, the rounded remainder, and the rest
+struct Split3 { bf16x8 p[3]; };
+__device__ __forceinline__ void split2(f32x2 v, bf16x2 (&p)[3]) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NTW; ++nt) acc2[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bq[4][NTW], af[2][MT];
-    auto load_b = [&](unsigned off, float (&dst)[NTW]) {
-#pragma unroll
-        for (int nt = 0; nt < NTW; ++nt) dst[nt] = buf_load(r_f1, off + ch4 + 64u * nt);
-    };
-    // The point tiles' fragments are 16 rows of G apart (33 * 256 bytes): from a base the compiler has to take as it
-    // is (the empty asm), with constant offsets, two of them leave in one LDS instruction.  Left to itself the loop
-    // optimiser rebases the reads on the end of the range and spends an address addition on every one of them.
-    typedef const __attribute__((address_space(3))) float* lds_cfp;
-    lds_cfp gbase = (lds_cfp)G + lr * GST + lg;
-    auto read_a = [&](lds_cfp gc, float (&dst)[MT]) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) dst[mt] = gc[16 * mt * GST];
-    };
-    load_b(q_off[lg], bq[0]); load_b(q_off[4 + lg], bq[1]); load_b(q_off[8 + lg], bq[2]);
-    unsigned off_next = q_off[12 + lg];
-    read_a(gbase, af[0]);
-#pragma unroll 1
-    for (int ks0 = 0; ks0 < NMT * 4; ks0 += 4) {
-        lds_cfp gstep = gbase + 4 * ks0;
-        asm volatile("" : "+v"(gstep));
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int ks = ks0 + s;
-            load_b(off_next, bq[(s + 3) & 3]);
-            off_next = q_off[4 * (ks + 4) + lg];
-            read_a(gstep + 4 * (s + 1), af[(s + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NTW; ++nt) acc2[mt][nt] = mma4(af[s & 1][mt], bq[s][nt], acc2[mt][nt]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const unsigned off = rowoff[16 * mt + 4 * lg + e] + ch4;
-#pragma unroll
-            for (int nt = 0; nt < NTW; ++nt)
-                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(acc2[mt][nt][e], r_d2, (int)(off + 64u * nt), 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);                   // one tile's table reads at a time (left alone, all are hoisted)
+    for (int k = 0; k < 3; ++k) {
+        p[k] = __builtin_convertvector(v, bf16x2);
+        v -= __builtin_convertvector(p[k], f32x2);
     }
 }
+__device__ __forceinline__ Split3 split8(const float (&v)[8]) {
+    Split3 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        bf16x2 p[3];
+        split2(f32x2{v[2 * i], v[2 * i + 1]}, p);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) { r.p[k][2 * i] = p[k][0]; r.p[k][2 * i + 1] = p[k][1]; }
+    }
+    return r;
+}
+// acc += a * b to fp32's precision: the six partial products down to 2^-24, small ones first
+__device__ __forceinline__ f32x4 mma6(const Split3& a, const Split3& b, f32x4 c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[2], b.p[0], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[0], b.p[2], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[1], b.p[1], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[1], b.p[0], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[0], b.p[1], c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[0], b.p[0], c, 0, 0, 0);
+}
+// LDS byte of (point, plane 0, block of 16 query ranks) of G: 32-byte blocks, XOR-swizzled by the point so that reads along
+// the points (8 of them, one block each) and along the queries spread over all banks
+__device__ __forceinline__ unsigned g_at(int row, int block) { return (unsigned)(row * G_ROW + ((block ^ (row & 7)) << 5)); }
 
 #ifdef CORR_TRACE
 // trace builds: thread 0 adds up the 100 MHz wall clock per phase (a barrier in front of every reading, so a phase's
@@ -235,20 +244,21 @@ __device__ __forceinline__ void rows_gradient(const float* G, const unsigned* ro
 #define BT(slot) do {} while (0)
 #endif
 // One item, levels lv_lo .. lv_hi - 1, d f1 into share `part` (whole items: all levels, share 0).
-// NMT: 16-query tiles the item fills (1..8)
-// KT: the window side 2r + 1 as a constant (the largest radius, the usual one), or 0: taken from the arguments
+// KT: the footprint's taps per axis, 2r + 1, as a constant (the largest radius, the usual one), or 0: taken from the arguments
 // NTW: 16-channel tiles per wave: 2 (a workgroup covers 256 channels at a time), or 1 for D <= 128, so that all
 // eight waves have channels to work on
-template <int NMT, int KT, int NTW>
+template <int KT, int NTW>
 __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned char* smem, const int4 item, const int k,
                                               const int lv_lo, const int lv_hi, const int part) {
-    float* G = reinterpret_cast<float*>(smem);                   // [CH][GST]
-    // byte offset of the feature row (pixel * D * 4) of each point of the pass / of each query slot; BAD_OFF: outside the level / empty
-    unsigned* rowoff = reinterpret_cast<unsigned*>(smem + CH * GST * 4);   // [CH + pad]
-    unsigned* q_off = rowoff + CH + TAB_PAD;                                // [128 + pad]
-    float* q_cx = reinterpret_cast<float*>(q_off + CORR_GROUP + TAB_PAD);
-    float* q_cy = q_cx + CORR_GROUP;
-    float* taps = q_cy + CORR_GROUP;                             // [K*K][128] tap gradients of the level in work, one column per query
+    unsigned* rowoff = reinterpret_cast<unsigned*>(smem + I_ROW);
+    unsigned* q_off = reinterpret_cast<unsigned*>(smem + I_Q);
+    float* q_cx = reinterpret_cast<float*>(smem + I_CX);
+    float* q_cy = reinterpret_cast<float*>(smem + I_CY);
+    unsigned* q_pix = reinterpret_cast<unsigned*>(smem + I_PIX);
+    int* q_col = reinterpret_cast<int*>(smem + I_COL);
+    int* hist = reinterpret_cast<int*>(smem + I_HIST);
+    float* taps = reinterpret_cast<float*>(smem + I_TAPS);
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lg = lane >> 4;
     const int n = item.z;
@@ -258,37 +268,75 @@ __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned cha
 #endif
     int b, u, v;
     corr_cell_coords(a.g, item.x, &b, &u, &v);
-    u += a.g.u_min; v += a.g.v_min;
+    const int cell_x = (u + a.g.u_min) * (1 << CORR_LOG_CX), cell_y = (v + a.g.v_min) * (1 << CORR_LOG_CY);
     const int K = KT ? KT : 2 * a.r + 1, KK = K * K, D = a.D;
     const int R = (K - 1) / 2;
-    if (tid < CORR_GROUP + TAB_PAD) {
-        int pix = -1;
-        float2 xy = make_float2(0.f, 0.f);
-        if (tid < n) { pix = a.perm[item.y + tid] - b * a.HW; xy = a.sorted_c[item.y + tid]; }
-        q_off[tid] = pix >= 0 ? (unsigned)pix * (unsigned)D * 4u : BAD_OFF;
-        if (tid < CORR_GROUP) { q_cx[tid] = xy.x; q_cy[tid] = xy.y; }
+    // the item's queries, ranked by target column
+    {
+        const bool real = tid < n;
+        int rx = 0, rank = 0;
+        unsigned pix = 0;
+        float2 xy = {0.f, 0.f};
+        if (real) {
+            xy = a.sorted_c[item.y + tid];
+            pix = (unsigned)(a.perm[item.y + tid] - b * a.HW);
+            rx = ((int)floorf(xy.x) - cell_x) & ((1 << CORR_LOG_CX) - 1);
+        }
+        if (tid < CORR_GROUP) { q_pix[tid] = BAD_OFF; q_off[tid] = BAD_OFF; }
+        if (tid >= NTI - 16) hist[tid - (NTI - 16)] = 0;
+        __syncthreads();
+        if (real) rank = atomicAdd(&hist[rx], 1);
+        __syncthreads();
+        if (real) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) rank += i < rx ? hist[i] : 0;
+            q_cx[rank] = xy.x; q_cy[rank] = xy.y; q_pix[rank] = pix * 4u;
+            q_col[rank] = rx; q_off[rank] = pix * (unsigned)D * 4u;
+        }
+        __syncthreads();
     }
-    if (tid < TAB_PAD) rowoff[CH + tid] = BAD_OFF;
-    __syncthreads();
+    const int tiles = (n + 15) >> 4;
+    // lane t: leftmost and rightmost target column of tile t
+    const int tx0 = q_col[min(16 * (lane & (QT - 1)), n - 1)], tx1 = q_col[min(16 * (lane & (QT - 1)) + 15, n - 1)];
     BT(0);
     const __amdgpu_buffer_rsrc_t r_f1 = rsrc_of(a.f1 + (size_t)b * a.HW * D, (size_t)a.HW * D);
     const __amdgpu_buffer_rsrc_t r_d1 = rsrc_of(a.d_f1 + ((size_t)part * a.B + b) * a.HW * D, (size_t)a.HW * D);
 
     for (int cg = 0; cg < D; cg += 128 * NTW) {                  // channel groups of 128 * NTW: 16 * NTW per wave
         const int ch = cg + wave * (16 * NTW) + lr;              // this lane's channel of tile nt: ch + 16 * nt
+        const unsigned ch4 = (unsigned)ch * 4u;
+        // the first contraction deals a wave's channels out alternately (tile nt, column lr: channel NTW * lr + nt), so that a lane's
+        // are next to each other in memory
+        const unsigned ca4 = (unsigned)(cg + wave * (16 * NTW) + NTW * lr) * 4u;
         const bool wave_on = cg + wave * (16 * NTW) < D;         // uniform; D is a multiple of 32
-        f32x4 acc1[NMT][NTW];
+        f32x4 acc1[QT][NTW];
 #pragma unroll
-        for (int mt = 0; mt < NMT; ++mt)
+        for (int t = 0; t < QT; ++t)
 #pragma unroll
-            for (int nt = 0; nt < NTW; ++nt) acc1[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int nt = 0; nt < NTW; ++nt) acc1[t][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // f1 as the second contraction's B operand: queries 32 * s + 8 * lg + i of this lane's channels
+        Split3 f1f[QT / 2][NTW];
+        if (wave_on) {
+#pragma unroll
+            for (int s = 0; s < QT / 2; ++s) {
+                float x[NTW][8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const unsigned off = q_off[32 * s + 8 * lg + i] + ch4;
+#pragma unroll
+                    for (int nt = 0; nt < NTW; ++nt) x[nt][i] = buf_load(r_f1, off + 64u * nt);
+                }
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) f1f[s][nt] = split8(x[nt]);
+            }
+        }
 
         // Tap gradients of one level, from d_out straight into LDS (no registers in between, so the loads can fly
         // under a contraction): wave = (half of the queries, every fourth tap), lane = query.  The level's K*K
         // planes of this batch item are one buffer: the lane's pixel is the vector offset (an empty slot's lies
         // past the end and lands as zero), the tap's plane a scalar offset; a wave's 64 values land at
         // taps[t][64 * half + lane].
-        const unsigned tq_off = (tid & (CORR_GROUP - 1)) < n ? q_off[tid & (CORR_GROUP - 1)] / (unsigned)D : BAD_OFF;   // pixel * 4
+        const unsigned tq_off = q_pix[tid & (CORR_GROUP - 1)];   // pixel * 4
         int tv_level = -1;
         auto load_taps = [&](int lv) {
             const uint64_t base = reinterpret_cast<uint64_t>(a.d_out + ((size_t)(b * a.L + lv) * KK) * a.HW);
@@ -297,21 +345,22 @@ __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned cha
             rs[1] = __builtin_amdgcn_readfirstlane((int)((base >> 32) & 0xffffu));
             rs[2] = __builtin_amdgcn_readfirstlane(KK * a.HW * 4);
             rs[3] = __builtin_amdgcn_readfirstlane(0x00020000);
-            const unsigned lds0 = __builtin_amdgcn_readfirstlane(
-                (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)taps + (unsigned)(wave & 1) * 256u);
+            const unsigned to = __builtin_amdgcn_readfirstlane(lds0 + (unsigned)I_TAPS + (unsigned)(wave & 1) * 256u);
             for (int t = wave >> 1; t < KK; t += NTI / CORR_GROUP)
-                dma4(rs, __builtin_amdgcn_readfirstlane(lds0 + (unsigned)t * (CORR_GROUP * 4)), tq_off,
+                dma4(rs, __builtin_amdgcn_readfirstlane(to + (unsigned)t * (CORR_GROUP * 4)), tq_off,
                      __builtin_amdgcn_readfirstlane(t * a.HW * 4));
             tv_level = lv;
         };
         for (int l = lv_lo; l < lv_hi; ++l) {
             const int Hl = a.Hl[l], Wl = a.Wl[l];
-            const int CXL = max((1 << CORR_LOG_CX) >> l, 1), CYL = max((1 << CORR_LOG_CY) >> l, 1);
-            const int WSX = CXL + K, WSY = CYL + K, NPTS = WSX * WSY;
-            const int xs = ((u << CORR_LOG_CX) >> l) - R, ys = ((v << CORR_LOG_CY) >> l) - R;
-            if (!(xs + WSX - 1 >= 0 && xs <= Wl - 1 && ys + WSY - 1 >= 0 && ys <= Hl - 1)) continue;   // all padding (uniform)
+            // the cell's window: points are numbered the same way whatever queries the item holds, so that a query's sums do
+            // not depend on its company (bits)
+            const int xs = (cell_x >> l) - R, ys = (cell_y >> l) - R;
+            const int wx = max((1 << CORR_LOG_CX) >> l, 1) + K, wy = max((1 << CORR_LOG_CY) >> l, 1) + K;
+            if (!(xs + wx - 1 >= 0 && xs <= Wl - 1 && ys + wy - 1 >= 0 && ys <= Hl - 1)) continue;   // all padding (uniform)
             const __amdgpu_buffer_rsrc_t r_f2 = rsrc_of(a.f2[l] + (size_t)b * Hl * Wl * D, (size_t)Hl * Wl * D);
             const __amdgpu_buffer_rsrc_t r_d2 = rsrc_of(a.d_f2[l] + (size_t)b * Hl * Wl * D, (size_t)Hl * Wl * D);
+            const float iwy = 1.0f / (float)wy;
             // this level's tap gradients: on their way into LDS since the previous level's last pass, or loaded now
             // (the first level, or one after a level that was all padding)
             if (tv_level != l) {
@@ -320,24 +369,45 @@ __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned cha
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's part has landed; the passes' barriers cover the others'
             BT(1);
-            for (int r0 = 0; r0 < NPTS; r0 += CH) {
+            // lane t: the points that the footprints of tile t reach, columns of the window from its leftmost to its rightmost one
+            const int first_pt = (tx0 >> l) * wy, end_pt = (lane & (QT - 1)) < tiles ? ((tx1 >> l) + K + 1) * wy : 0;
+            // bit t: tile t's footprints reach points p .. p + len - 1 (uniform)
+            auto reached = [&](int p, int len) { return (unsigned)__ballot(p < end_pt && p + len > first_pt) & ((1u << QT) - 1u); };
+            const int begin = __builtin_amdgcn_readlane(first_pt, 0), npts = __builtin_amdgcn_readlane(end_pt, tiles - 1);   // of the whole item
+            for (int r0 = begin / CH * CH; r0 < npts; r0 += CH) {
                 __syncthreads();                                 // the previous pass no longer reads G or rowoff
                 {
-                    float4* g4 = reinterpret_cast<float4*>(G);
-                    for (int i = tid; i < CH * GST / 4; i += NTI) g4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (tid < CH) {
-                        const int row = r0 + tid, wy = row / WSX, wx = row - wy * WSX;
-                        const int y = ys + wy, x = xs + wx;
-                        rowoff[tid] = (row < NPTS && y >= 0 && y < Hl && x >= 0 && x < Wl) ? (unsigned)(y * Wl + x) * (unsigned)D * 4u : BAD_OFF;
+                    u32x4* g4 = reinterpret_cast<u32x4*>(smem + I_G);
+                    const int used = (min(CH, npts - r0) + 31 & ~31) < CH ? min(CH, npts - r0) + 31 & ~31 : CH;   // whole runs of points
+                    for (int i = tid; i < used * (G_ROW / 16); i += NTI) g4[i] = u32x4{0u, 0u, 0u, 0u};
+                    if (tid < TAB) {
+                        const int p = r0 + tid, px = (int)(((float)p + 0.5f) * iwy), py = p - px * wy;     // p < 512: exact
+                        const int y = ys + py, x = xs + px;
+                        rowoff[tid] = (tid < CH && p < npts && y >= 0 && y < Hl && x >= 0 && x < Wl) ? (unsigned)(y * Wl + x) * (unsigned)D * 4u : BAD_OFF;
                     }
                 }
                 __syncthreads();
                 BT(2);
+                const int rows = min(CH, npts - r0), nks = (rows + 31) >> 5;
+                // f2 rows of a run of 32 points as the first contraction's B operand: points 8 * lg .. + 7 of this lane's channels.
+                typedef unsigned raw_t __attribute__((ext_vector_type(NTW)));
+                raw_t x[8];
+                auto load_b = [&](int ks) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const u32x4 off = *reinterpret_cast<const u32x4*>(rowoff + 32 * ks + 8 * lg + 4 * h);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if constexpr (NTW == 2) x[4 * h + i] = __builtin_amdgcn_raw_buffer_load_b64(r_f2, (int)(off[i] + ca4), 0, 0);
+                            else x[4 * h + i] = __builtin_amdgcn_raw_buffer_load_b32(r_f2, (int)(off[i] + ca4), 0, 0);
+                        }
+                    }
+                };
                 {
-                    // footprint weights into G: thread = (query, quarter of the footprint columns).  Point (pu, pv)
+                    // footprint weights into G: thread = (query, every fourth footprint column).  Point (pu, pv)
                     // collects the taps (pu - du, pv - dv), du, dv in {0, 1}, with their corner weights; every
                     // element of G has one writer, so G (and with it d f1) is the same bits on every call.
-                    const int q = tid & (CORR_GROUP - 1), part = tid >> 7;
+                    const int q = tid & (CORR_GROUP - 1), quarter = tid >> 7;
                     if (q < n) {
                         const float inv = __uint_as_float((uint32_t)(127 - l) << 23);
                         const float cxl = q_cx[q] * inv, cyl = q_cy[q] * inv;
@@ -345,27 +415,36 @@ __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned cha
                         const float fx = cxl - flx, fy = cyl - fly;
                         const int rx = (int)flx - R - xs, ry = (int)fly - R - ys;
                         const float wx1 = fx * a.scale, wx0 = a.scale - wx1;
-                        const int p0 = part * (K + 1) / 4, p1 = (part + 1) * (K + 1) / 4;
                         const float* dp = taps + q;
-                        float* gq = G + q;
-                        for (int pu = p0; pu < p1; ++pu) {
+                        const unsigned gq = lds0 + (unsigned)(I_G + (q & 15) * 2);
+                        for (int pu = quarter; pu <= K; pu += 4) {
+                            const int row0 = (rx + pu) * wy + ry - r0;                   // of the column's first point
+                            if (row0 <= -(K + 1) || row0 >= CH) continue;                // none in this pass
                             // the column's horizontally weighted taps first (all LDS reads in flight at once), then its K + 1 points
                             const float w0 = pu < K ? wx0 : 0.f, w1 = pu >= 1 ? wx1 : 0.f;
                             const float* c0 = dp + min(pu, K - 1) * K * CORR_GROUP;
                             const float* c1 = dp + max(pu - 1, 0) * K * CORR_GROUP;
-                            float t[MAXK + 1];
+                            float t[MAXK + 2];
+                            t[0] = 0.f;
 #pragma unroll
                             for (int j = 0; j < MAXK; ++j) {
                                 const int jj = min(j, K - 1);
-                                t[j] = j < K ? c0[jj * CORR_GROUP] * w0 + c1[jj * CORR_GROUP] * w1 : 0.f;
+                                t[j + 1] = j < K ? c0[jj * CORR_GROUP] * w0 + c1[jj * CORR_GROUP] * w1 : 0.f;
                             }
-                            t[MAXK] = 0.f;
-                            int rr = ry * WSX + rx + pu - r0;
+                            t[MAXK + 1] = 0.f;
 #pragma unroll
-                            for (int pv = 0; pv <= MAXK; ++pv) {
-                                const float tprev = pv >= 1 ? t[pv - 1] : 0.f;
-                                if (pv <= K && (unsigned)rr < (unsigned)CH) gq[rr * GST] = t[pv] + fy * (tprev - t[pv]);
-                                rr += WSX;
+                            for (int pv = 0; pv <= MAXK; pv += 2) {
+                                bf16x2 p[3];
+                                split2(f32x2{t[pv + 1] + fy * (t[pv] - t[pv + 1]), t[pv + 2] + fy * (t[pv + 1] - t[pv + 2])}, p);
+#pragma unroll
+                                for (int e = 0; e < 2; ++e) {
+                                    const int row = row0 + pv + e;
+                                    if (pv + e <= K && (unsigned)row < (unsigned)CH) {
+                                        lds_bf16 to = (lds_bf16)(uintptr_t)(gq + g_at(row, q >> 4));
+#pragma unroll
+                                        for (int k = 0; k < 3; ++k) to[k * (G_PLANE / 2)] = p[k][e];
+                                    }
+                                }
                             }
                         }
                     }
@@ -373,72 +452,106 @@ __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned cha
                 __syncthreads();
                 BT(3);
                 if (wave_on) {
-                    const int rows = min(CH, NPTS - r0);
-                    const unsigned ch4 = (unsigned)ch * 4u;
-                    float bq[4][NTW];
-                    // d f1 += G^T x f2 rows.  k-step ks takes points 4*ks + lg.  Software pipeline, pinned by the
-                    // scheduling barriers: the f2 values of step ks + 3, the table entry of step ks + 4 and the G
-                    // fragments of step ks + 1 are on their way while the matrix cores work on step ks.  Steps
-                    // past the last one find BAD_OFF in the table (zeros) and rows of zeros in G.
-                    const int nks = (rows + 3) >> 2;
-                    {
-                        float af[2][NMT];
-                        auto load_b = [&](unsigned off, float (&dst)[NTW]) {
+                    // d f1 += G^T x f2 rows, 32 points at a time.  A operand: 16 ranks x 8 consecutive points per lane group
+                    // through the transposing read (lane i of 16 addresses 4 ranks of point i / 4, twice).
+                    Split3 bf[NTW];
+                    auto split_b = [&]() {
 #pragma unroll
-                            for (int nt = 0; nt < NTW; ++nt) dst[nt] = buf_load(r_f2, off + ch4 + 64u * nt);
-                        };
-                        auto read_a = [&](int ks, float (&dst)[NMT]) {
-                            const float* gr = G + (4 * ks + lg) * GST + lr;
+                        for (int nt = 0; nt < NTW; ++nt) {
+                            float f[8];
 #pragma unroll
-                            for (int mt = 0; mt < NMT; ++mt) dst[mt] = gr[16 * mt];
-                        };
-                        load_b(rowoff[lg], bq[0]); load_b(rowoff[4 + lg], bq[1]); load_b(rowoff[8 + lg], bq[2]);
-                        unsigned off_next = rowoff[12 + lg];
-                        read_a(0, af[0]);
+                            for (int i = 0; i < 8; ++i) { const unsigned w = x[i][nt]; f[i] = __uint_as_float(w); }
+                            bf[nt] = split8(f);
+                        }
+                    };
+                    load_b(0);
+                    split_b();
 #pragma unroll 1
-                        for (int ks0 = 0; ks0 < nks; ks0 += 4) {
+                    for (int ks = 0; ks < nks; ++ks) {
+                        load_b(min(ks + 1, nks - 1));            // always: a load that may not be issued would be waited for early
+                        const unsigned on = reached(r0 + 32 * ks, 32);
+                        // rows past the pass (the last run is half a one) meet zeros of f2: any finite row will do
+                        const int ra = min(32 * ks + 8 * lg, CH - 8) + (lr >> 2);
+                        // blocks are 32-byte parts of an aligned 256 bytes: the swizzle is one exclusive or
+                        const unsigned ga0 = lds0 + (unsigned)(I_G + ra * G_ROW + 8 * (lr & 3)) + ((unsigned)(lr >> 2) << 5);
+                        const unsigned ga1 = lds0 + (unsigned)(I_G + (ra + 4) * G_ROW + 8 * (lr & 3)) + ((unsigned)(4 + (lr >> 2)) << 5);
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) {
-                                const int ks = ks0 + s;
-                                load_b(off_next, bq[(s + 3) & 3]);
-                                off_next = rowoff[4 * (ks + 4) + lg];
-                                read_a(ks + 1, af[(s + 1) & 1]);
-                                __builtin_amdgcn_sched_barrier(0);
+                        for (int t = 0; t < QT; ++t) {
+                            if (on >> t & 1u) {
+                                Split3 af;
 #pragma unroll
-                                for (int mt = 0; mt < NMT; ++mt)
+                                for (int k = 0; k < 3; ++k) {
+                                    const s16x4 u0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)((ga0 ^ (unsigned)(t << 5)) + k * G_PLANE));
+                                    const s16x4 u1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)((ga1 ^ (unsigned)(t << 5)) + k * G_PLANE));
+                                    const bf16x4 v0 = __builtin_bit_cast(bf16x4, u0), v1 = __builtin_bit_cast(bf16x4, u1);
+                                    af.p[k] = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+                                }
 #pragma unroll
-                                    for (int nt = 0; nt < NTW; ++nt) acc1[mt][nt] = mma4(af[s & 1][mt], bq[s][nt], acc1[mt][nt]);
-                                __builtin_amdgcn_sched_barrier(0);
+                                for (int nt = 0; nt < NTW; ++nt) acc1[t][nt] = mma6(af, bf[nt], acc1[t][nt]);
                             }
                         }
+                        split_b();
                     }
                 }
                 BT(4);
                 // the next level's tap gradients start to move under the second contraction of this level's last
                 // pass (every wave is past the pass's scatter, the last reader of the current ones)
-                if (r0 + CH >= NPTS && l + 1 < lv_hi) load_taps(l + 1);
+                if (r0 + CH >= npts && l + 1 < lv_hi) load_taps(l + 1);
                 if (wave_on) {
-                    const int rows = min(CH, NPTS - r0);
-                    const unsigned ch4 = (unsigned)ch * 4u;
-                    // d f2_l rows of this pass = G x f1, over as many 16-point tiles as the pass has rows (rounded up to odd)
-                    const int tiles = (rows + 15) >> 4;
-                    if (tiles <= 3) rows_gradient<NMT, 3, NTW>(G, rowoff, q_off, r_f1, r_d2, ch4, lr, lg);
-                    else if (tiles <= 5) rows_gradient<NMT, 5, NTW>(G, rowoff, q_off, r_f1, r_d2, ch4, lr, lg);
-                    else if (tiles <= 7) rows_gradient<NMT, 7, NTW>(G, rowoff, q_off, r_f1, r_d2, ch4, lr, lg);
-                    else rows_gradient<NMT, MTC, NTW>(G, rowoff, q_off, r_f1, r_d2, ch4, lr, lg);
+                    // d f2_l rows of this pass = G x f1, 16 points at a time, then out through atomics
+                    const int ntile = (rows + 15) >> 4;
+                    const unsigned sw = (unsigned)(lr & 7);
+#pragma unroll 1
+                    for (int m = 0; m < ntile; ++m) {
+                        const unsigned on = reached(r0 + 16 * m, 16);
+                        if (on == 0) continue;
+                        const unsigned ga = lds0 + (unsigned)(I_G + (16 * m + lr) * G_ROW + (lg & 1) * 16) + (((unsigned)(lg >> 1) ^ sw) << 5);
+                        f32x4 acc2[NTW];
+#pragma unroll
+                        for (int nt = 0; nt < NTW; ++nt) acc2[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int s = 0; s < QT / 2; ++s) {
+                            if (on >> (2 * s) & 3u) {
+                                Split3 af;
+#pragma unroll
+                                for (int k = 0; k < 3; ++k)
+                                    af.p[k] = __builtin_bit_cast(bf16x8, *(lds_u32x4)(uintptr_t)((ga ^ (unsigned)(s << 6)) + k * G_PLANE));
+#pragma unroll
+                                for (int nt = 0; nt < NTW; ++nt) acc2[nt] = mma6(af, f1f[s][nt], acc2[nt]);
+                            }
+                        }
+                        if constexpr (NTW == 2) {
+                            // lane groups 2g and 2g + 1 hold 16 channels each of different points: they swap a tile, so that one
+                            // atomic covers 128 bytes of each of two rows (a whole line) instead of 64 of each of four
+                            const u32x4 off0 = *reinterpret_cast<const u32x4*>(rowoff + 16 * m + 4 * (lg & 2));
+                            const u32x4 off1 = *reinterpret_cast<const u32x4*>(rowoff + 16 * m + 4 * (lg & 2) + 4);
+                            const unsigned c4 = (unsigned)(cg + wave * 32 + 16 * (lg & 1) + lr) * 4u;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const auto two = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc2[0][e]), __float_as_uint(acc2[1][e]), false, false);
+                                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(__uint_as_float(two[0]), r_d2, (int)(off0[e] + c4), 0, 0);
+                                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(__uint_as_float(two[1]), r_d2, (int)(off1[e] + c4), 0, 0);
+                            }
+                        } else {
+                            const u32x4 off = *reinterpret_cast<const u32x4*>(rowoff + 16 * m + 4 * lg);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(acc2[0][e], r_d2, (int)(off[e] + ch4), 0, 0);
+                        }
+                    }
                 }
                 BT(5);
             }
         }
         if (wave_on) {
 #pragma unroll
-            for (int mt = 0; mt < NMT; ++mt)
+            for (int t = 0; t < QT; ++t)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const unsigned off = q_off[16 * mt + 4 * lg + e] + (unsigned)ch * 4u;
-#pragma unroll
-                    for (int nt = 0; nt < NTW; ++nt)
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc1[mt][nt][e]), r_d1, (int)(off + 64u * nt), 0, 0);
+                    const unsigned off = q_off[16 * t + 4 * lg + e] + ca4;
+                    if constexpr (NTW == 2)
+                        __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(acc1[t][0][e]), __float_as_uint(acc1[t][1][e])}, r_d1, (int)off, 0, 0);
+                    else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc1[t][0][e]), r_d1, (int)off, 0, 0);
                 }
         }
     }
@@ -446,7 +559,7 @@ __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned cha
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #ifdef CORR_TRACE
     BT(6);
-    if (tid == 0 && a.trace) { for (int i = 0; i < 7; ++i) a.trace[(size_t)k * 8 + i] = tacc[i]; a.trace[(size_t)k * 8 + 7] = NMT; }
+    if (tid == 0 && a.trace) { for (int i = 0; i < 7; ++i) a.trace[(size_t)k * 8 + i] = tacc[i]; a.trace[(size_t)k * 8 + 7] = tiles; }
 #endif
 }
 
@@ -458,8 +571,8 @@ __device__ __forceinline__ void bwd_item_body(const BwdItemArgs& a, unsigned cha
 // one waits for a unit of its own), and the end of the launch is shared out item by item.  Handing out the full
 // items first and the small ones last was measured too: it costs more in L2 misses than it gains at the end.
 __global__ __launch_bounds__(NTI, 2) void bwd_item_kernel(BwdItemArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int s_next;
+    extern __shared__ __align__(256) unsigned char smem[];
+    int& s_next = *reinterpret_cast<int*>(smem + I_NEXT);
     int xcd = (int)blockIdx.x & 7, tried = 0;
     const int n_items = *a.n_items;
     const int share = (n_items + 8 * CORR_XCD_RUN - 1) / (8 * CORR_XCD_RUN) * CORR_XCD_RUN;   // item positions per queue
@@ -478,24 +591,16 @@ __global__ __launch_bounds__(NTI, 2) void bwd_item_kernel(BwdItemArgs a) {
         const int k = corr_item_of_workgroup(ipos * 8 + xcd);
         if (k >= n_items) continue;
         const int4 item = a.items[k];
-        const int tiles = (item.z + 15) >> 4;
         // parts = L: one level each; parts = 2 (and L > 2): level 0, and the rest
         const int lv_lo = a.parts > 1 ? part : 0;
         const int lv_hi = a.parts == 1 || (a.parts == 2 && part == 1) ? a.L : part + 1;
-#define CORR_BWD_CASE(N, KT, NTW) case N: bwd_item_body<N, KT, NTW>(a, smem, item, k, lv_lo, lv_hi, part); break;
-#define CORR_BWD_SWITCH(KT, NTW)                                                                              \
-        switch (tiles) {                                                                                      \
-            CORR_BWD_CASE(1, KT, NTW) CORR_BWD_CASE(2, KT, NTW) CORR_BWD_CASE(3, KT, NTW) CORR_BWD_CASE(4, KT, NTW) \
-            CORR_BWD_CASE(5, KT, NTW) CORR_BWD_CASE(6, KT, NTW) CORR_BWD_CASE(7, KT, NTW)                     \
-            default: bwd_item_body<8, KT, NTW>(a, smem, item, k, lv_lo, lv_hi, part); break;                  \
-        }
         if (a.D <= 128) {
-            if (a.r == CORR_R) { CORR_BWD_SWITCH(MAXK, 1) } else { CORR_BWD_SWITCH(0, 1) }
+            if (a.r == CORR_R) bwd_item_body<MAXK, 1>(a, smem, item, k, lv_lo, lv_hi, part);
+            else bwd_item_body<0, 1>(a, smem, item, k, lv_lo, lv_hi, part);
         } else {
-            if (a.r == CORR_R) { CORR_BWD_SWITCH(MAXK, 2) } else { CORR_BWD_SWITCH(0, 2) }
+            if (a.r == CORR_R) bwd_item_body<MAXK, 2>(a, smem, item, k, lv_lo, lv_hi, part);
+            else bwd_item_body<0, 2>(a, smem, item, k, lv_lo, lv_hi, part);
         }
-#undef CORR_BWD_SWITCH
-#undef CORR_BWD_CASE
     }
 }
 

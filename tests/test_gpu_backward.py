@@ -268,3 +268,29 @@ def test_backward_error_paths():
                                   small.data_ptr(), 64, None)
     assert st == b.CORR_ERR_INVALID_ARG
     pyr.destroy()
+
+
+@pytest.mark.parametrize("n,D,r", [(1, 32, 4), (15, 96, 1), (16, 160, 4), (17, 128, 2), (127, 256, 3), (128, 288, 4), (129, 64, 4), (250, 544, 2)])
+def test_items_of_every_fill(n, D, r):
+    """One target cell holding n queries (items of 1 to 128 of them, whole and partial 16-query tiles) at its edges and inside
+    it, next to the level's border; channel counts that end inside a wave's 32 and a workgroup's 128 or 256."""
+    b = _binding()
+    dev = torch.device("cuda:0")
+    H, W, L = 16, 24, 4
+    f1, f2, c = synth.small_case(77 + n, 1, H, W, D, flow_range=1.0)
+    rng = np.random.default_rng(n)
+    xy = np.stack([rng.uniform(0.0, 16.0, n), rng.uniform(8.0, 16.0, n)]).astype(np.float32)
+    xy[:, 0] = (15.96875, 15.96875)                     # the cell's last column and row, with a fraction
+    xy[0, n // 2] = 0.0
+    c[:] = np.float32(-1e6)
+    c.reshape(2, H * W)[:, rng.permutation(H * W)[:n]] = xy
+    d_out = rng.standard_normal((1, L * (2 * r + 1) ** 2, H, W)).astype(np.float32)
+    want1, want2 = oracle.backward(f1, f2, c, d_out, L=L, r=r)
+    t1, t2, tc, tg = (torch.from_numpy(a).to(dev) for a in (f1, f2, c, d_out))
+    pyr = b.corr_pyramid_build(t1, t2, L=L, reps=b.CORR_REP_F32)
+    print("items of every fill", n, D, r, flush=True)
+    g1, g2 = b.corr_sample_backward(pyr, tc, tg, r=r)
+    torch.cuda.synchronize()
+    _check(g1, want1, "d_fmap1 n=%d D=%d r=%d" % (n, D, r))
+    _check(g2, want2, "d_fmap2 n=%d D=%d r=%d" % (n, D, r))
+    pyr.destroy()
