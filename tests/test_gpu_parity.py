@@ -383,3 +383,23 @@ def test_error_paths():
     big = b.corr_full_volume_bytes(1, 540, 960, 4)
     free_b, _ = torch.cuda.mem_get_info()
     assert big > free_b
+
+
+@pytest.mark.parametrize("B,H,W,D,L,r,nhwc", [(1, 8, 8, 32, 4, 4, 0), (1, 8, 17, 64, 4, 3, 1), (2, 16, 12, 96, 2, 1, 0),
+                                              (1, 9, 71, 256, 1, 4, 0), (3, 33, 10, 160, 3, 2, 1), (1, 35, 66, 32, 4, 4, 0)])
+def test_full_volume_tiles_and_remainders(B, H, W, D, L, r, nhwc):
+    """Full-volume mode where its kernels' tiles end: 64 x 128 of the product, 8 x 32 of the pooling, 16 queries of the
+    sampling; levels of one row or column, every radius, both layouts."""
+    b = _binding()
+    dev = torch.device("cuda:0")
+    f1, f2, c = synth.small_case(900 + H * W, B, H, W, D, flow_range=6.0)
+    c[0, :, 0, 0] = (-0.5, -0.25)                      # half outside
+    c[0, :, 0, 1] = (W - 0.5, H - 0.25)
+    c[0, :, 1, 0] = np.float32("nan")
+    ref = oracle.lookup(f1, f2, c, L=L, r=r)
+    t1, t2, tc = (torch.from_numpy(a).to(dev) for a in (f1, f2, c))
+    pyr = b.corr_pyramid_build(t1, t2, L=L, reps=b.CORR_REP_F32)
+    got = b.corr_sample(t1, pyr, tc, r=r, mode=b.CORR_MODE_FULLVOLUME, layout=b.CORR_OUT_NHWC if nhwc else b.CORR_OUT_NCHW)
+    got = got.cpu().numpy()
+    _check(np.moveaxis(got, 3, 1) if nhwc else got, ref, 1e-5, "full volume %dx%dx%d D=%d L=%d r=%d" % (B, H, W, D, L, r))
+    pyr.destroy()
