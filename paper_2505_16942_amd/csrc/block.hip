@@ -40,17 +40,22 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// This file is compiled once per lookup radius (CORR_BLOCK_R = 1..4): window sizes, LDS sizes and
-// the tap loops are compile-time functions of it.
+// This file is compiled once per lookup radius (CORR_BLOCK_R = 1..4) and number of 32-channel chunks that a wave holds
+// query fragments of and a level's loop runs over (CORR_BLOCK_NC = 8, or 4 for D <= 128): window sizes, LDS sizes, the tap
+// loops and the chunk loop are compile-time functions of them.  Eight chunks for D = 128 loaded and multiplied four chunks of
+// zeros: a lookup on two 47 x 155 maps, D = 128, r = 3, took 46 us, with four chunks 34.
 #ifndef CORR_BLOCK_R
 #define CORR_BLOCK_R CORR_R
+#endif
+#ifndef CORR_BLOCK_NC
+#define CORR_BLOCK_NC (CORR_BLOCK_MAX_D / CORR_CHUNK)
 #endif
 #define CORR_CAT2(a, b) a##b
 #define CORR_CAT(a, b) CORR_CAT2(a, b)
 constexpr int R = CORR_BLOCK_R, K = 2 * R + 1, KK = K * K;
 constexpr int CX = 1 << CORR_LOG_CX, CY = 1 << CORR_LOG_CY;
 constexpr int NW = 4, NT = 64 * NW;
-constexpr int NCMAX = CORR_BLOCK_MAX_D / CORR_CHUNK;   // chunks of query fragments a wave holds
+constexpr int NCMAX = CORR_BLOCK_NC;   // chunks of query fragments a wave holds
 constexpr int LDS_BYTES = 160 * 1024;
 constexpr int META_BYTES = CORR_GROUP * 12;
 constexpr int LDS_DATA = LDS_BYTES - META_BYTES;       // ring slots and S
@@ -729,16 +734,21 @@ hipError_t launch_items(const corr_pyramid* p, const BinWs& ws, const LookupArgs
 
 }  // namespace
 
-#if defined(CORR_TRACE) && CORR_BLOCK_R == 4
+#if defined(CORR_TRACE) && CORR_BLOCK_R == 4 && CORR_BLOCK_NC == 8
 long long* g_corr_trace = nullptr;
 extern "C" void corr_debug_set_trace(long long* p) { g_corr_trace = p; }
 #endif
 
-hipError_t CORR_CAT(launch_block_r, CORR_BLOCK_R)(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s) {
-    const bool big = p->D > CORR_BLOCK_MAX_D, three = q.prec != CORR_PREC_BF16;
+hipError_t CORR_CAT(CORR_CAT(launch_block_r, CORR_BLOCK_R), CORR_CAT(_c, CORR_BLOCK_NC))(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s) {
+    const bool three = q.prec != CORR_PREC_BF16;
+#if CORR_BLOCK_NC * CORR_CHUNK < CORR_BLOCK_MAX_D
+#define CORR_LAUNCH(NHWC) (three ? launch_items<true, false, NHWC>(p, ws, q, s) : launch_items<false, false, NHWC>(p, ws, q, s))
+#else
+    const bool big = p->D > CORR_BLOCK_MAX_D;
 #define CORR_LAUNCH(NHWC)                                                                                    \
     (three ? (big ? launch_items<true, true, NHWC>(p, ws, q, s) : launch_items<true, false, NHWC>(p, ws, q, s))   \
            : (big ? launch_items<false, true, NHWC>(p, ws, q, s) : launch_items<false, false, NHWC>(p, ws, q, s)))
+#endif
     return q.nhwc ? CORR_LAUNCH(true) : CORR_LAUNCH(false);
 #undef CORR_LAUNCH
 }

@@ -133,10 +133,9 @@ std::atomic<int> g_split_levels_max{CORR_SPLIT_LEVELS_MAX_QUERIES};
 std::atomic<int> g_backward_form{CORR_BACKWARD_ITEMS};
 
 hipError_t launch_block(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s) {
-    return q.r == 1 ? launch_block_r1(p, ws, q, s)
-         : q.r == 2 ? launch_block_r2(p, ws, q, s)
-         : q.r == 3 ? launch_block_r3(p, ws, q, s)
-                    : launch_block_r4(p, ws, q, s);
+    static const BlockLauncher c4[CORR_R] = {launch_block_r1_c4, launch_block_r2_c4, launch_block_r3_c4, launch_block_r4_c4};
+    static const BlockLauncher c8[CORR_R] = {launch_block_r1_c8, launch_block_r2_c8, launch_block_r3_c8, launch_block_r4_c8};
+    return (p->D <= 4 * CORR_CHUNK ? c4 : c8)[q.r - 1](p, ws, q, s);
 }
 
 // planning pass + block kernel on workspace `ws`

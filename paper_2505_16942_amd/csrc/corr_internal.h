@@ -185,11 +185,16 @@ hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s
 hipError_t launch_fill_i32(int* dst, int value, size_t n, hipStream_t s);
 hipError_t launch_binning(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
 hipError_t launch_bin_stats(const corr_pyramid* p, const BinWs& ws, int r, hipStream_t s);
-// one instantiation of block.hip per lookup radius
-hipError_t launch_block_r1(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r2(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r3(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+// one instantiation of block.hip per lookup radius and number of channel chunks in its loop (_c4: D <= 128)
+typedef hipError_t (*BlockLauncher)(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r1_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r2_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r3_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r4_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r1_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r2_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r3_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+hipError_t launch_block_r4_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
 hipError_t launch_ondemand(const corr_pyramid* p, const LookupArgs& q, hipStream_t s);
 // gradient of the lookup (backward.hip): `ws` holds corr_backward_workspace_floats() floats
 size_t corr_backward_workspace_floats(int B, int H, int W, int D, int L);      // the gradient arrays

@@ -403,3 +403,17 @@ def test_full_volume_tiles_and_remainders(B, H, W, D, L, r, nhwc):
     got = got.cpu().numpy()
     _check(np.moveaxis(got, 3, 1) if nhwc else got, ref, 1e-5, "full volume %dx%dx%d D=%d L=%d r=%d" % (B, H, W, D, L, r))
     pyr.destroy()
+
+
+@pytest.mark.parametrize("D", [32, 128, 160])
+@pytest.mark.parametrize("r", [1, 2, 3, 4])
+def test_block_channel_loops(D, r):
+    """Both sides of the line between the block kernel's loops over four and eight channel chunks, and a loop of one, at
+    every radius and in both precisions."""
+    b = _binding()
+    f1, f2, c = synth.small_case(60 + D + r, 1, 19, 37, D, flow_range=8.0)
+    ref = oracle.lookup(f1, f2, c, L=4, r=r)
+    got, _ = _run(f1, f2, c, 4, r, b.CORR_MODE_BLOCK, reps=b.CORR_REP_SPLIT)
+    _check(got, ref, FP32_TOL, "block D=%d r=%d" % (D, r))
+    got, _ = _run(f1, f2, c, 4, r, b.CORR_MODE_BLOCK, prec=b.CORR_PREC_BF16, reps=b.CORR_REP_BF16)
+    _check(got, ref, None, "block bf16 D=%d r=%d" % (D, r), bound=bf16_bound(f1, f2, ref))
