@@ -11,10 +11,12 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libcorr_mi355x.so")
 OBJ_DIR = os.path.join(PKG, "_build")
-# (source, object name, extra flags); block.hip is built once per lookup radius and number of channel chunks
-SOURCES = [("corr_api.hip", "corr_api.o", []), ("features.hip", "features.o", []), ("binning.hip", "binning.o", []),
-           ("ondemand.hip", "ondemand.o", []), ("fullvol.hip", "fullvol.o", []), ("backward.hip", "backward.o", [])]
-SOURCES += [("block.hip", "block_r%d_c%d.o" % (r, nc), ["-DCORR_BLOCK_R=%d" % r, "-DCORR_BLOCK_NC=%d" % nc]) for nc in (8, 4) for r in (4, 3, 2, 1)]
+# (source, object name, extra flags); block.hip is built once per lookup radius and length of its channel loop (the longest
+# compilations first)
+SOURCES = [("block.hip", "block_r%d_c%d.o" % (r, nc), ["-DCORR_BLOCK_R=%d" % r, "-DCORR_BLOCK_NC=%d" % nc])
+           for nc in (8, 5, 4, 6, 3) for r in (4, 3, 2, 1)]
+SOURCES += [("corr_api.hip", "corr_api.o", []), ("features.hip", "features.o", []), ("binning.hip", "binning.o", []),
+            ("ondemand.hip", "ondemand.o", []), ("fullvol.hip", "fullvol.o", []), ("backward.hip", "backward.o", [])]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-I" + INCLUDE, "-I" + CSRC,
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]

@@ -6,9 +6,9 @@
 // level-0 pixels, up to 128 of its queries), processed level after level.  Wave w owns queries
 // 16w .. 16w+15 and 64+16w .. 64+16w+15 of the item as two MFMA column blocks (items of up to 64
 // queries use one).
-//   queries     : each wave loads the bf16 hi (and lo) fragments of its queries for 256 channels
+//   queries     : each wave loads the bf16 hi (and lo) fragments of its queries for up to 256 channels
 //                 once per item, straight from global memory into the MFMA B-operand layout, and
-//                 keeps them in registers for all levels (a larger D runs in groups of 256 channels
+//                 keeps them in registers for all levels (a larger D runs in groups of channels
 //                 with the fragments reloaded).
 //   contraction : S_l[pt][q] = <f2_l(window point pt), f1(query q)> over D.  The window is
 //                 streamed through LDS in units of (32-channel chunk, group of 16-point row blocks):
@@ -41,9 +41,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // This file is compiled once per lookup radius (CORR_BLOCK_R = 1..4) and number of 32-channel chunks that a wave holds
-// query fragments of and a level's loop runs over (CORR_BLOCK_NC = 8, or 4 for D <= 128): window sizes, LDS sizes, the tap
-// loops and the chunk loop are compile-time functions of them.  Eight chunks for D = 128 loaded and multiplied four chunks of
-// zeros: a lookup on two 47 x 155 maps, D = 128, r = 3, took 46 us, with four chunks 34.
+// query fragments of and a level's loop runs over (CORR_BLOCK_NC = 3, 4, 5, 6 or 8): window sizes, LDS sizes, the tap
+// loops and the chunk loop are compile-time functions of them.  A loop longer than D loads and multiplies chunks of zeros: a
+// lookup on two 47 x 155 maps, D = 128, r = 3, took 46 us with eight chunks and takes 34 with four.  Three is the shortest
+// that fills the ring.  Groups of six would spill the query fragments (D = 384 on a 200 x 300 map: 284 us, groups of four 263).
 #ifndef CORR_BLOCK_R
 #define CORR_BLOCK_R CORR_R
 #endif
@@ -741,10 +742,10 @@ extern "C" void corr_debug_set_trace(long long* p) { g_corr_trace = p; }
 
 hipError_t CORR_CAT(CORR_CAT(launch_block_r, CORR_BLOCK_R), CORR_CAT(_c, CORR_BLOCK_NC))(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s) {
     const bool three = q.prec != CORR_PREC_BF16;
-#if CORR_BLOCK_NC * CORR_CHUNK < CORR_BLOCK_MAX_D
+#if CORR_BLOCK_NC == 3 || CORR_BLOCK_NC == 6      // never for a larger D
 #define CORR_LAUNCH(NHWC) (three ? launch_items<true, false, NHWC>(p, ws, q, s) : launch_items<false, false, NHWC>(p, ws, q, s))
 #else
-    const bool big = p->D > CORR_BLOCK_MAX_D;
+    const bool big = p->D > CORR_BLOCK_NC * CORR_CHUNK;
 #define CORR_LAUNCH(NHWC)                                                                                    \
     (three ? (big ? launch_items<true, true, NHWC>(p, ws, q, s) : launch_items<true, false, NHWC>(p, ws, q, s))   \
            : (big ? launch_items<false, true, NHWC>(p, ws, q, s) : launch_items<false, false, NHWC>(p, ws, q, s)))

@@ -132,10 +132,26 @@ struct Profiler {
 std::atomic<int> g_split_levels_max{CORR_SPLIT_LEVELS_MAX_QUERIES};
 std::atomic<int> g_backward_form{CORR_BACKWARD_ITEMS};
 
+// The block kernel's channel loop has a fixed length; chunks past the last one are loaded and multiplied as zeros, so the
+// length with the fewest chunks in all is taken.  Up to 256 channels that is the shortest loop that holds D.  Beyond, D runs
+// in groups of 4, 5 or 8 chunks, whose times per chunk are 18, 16 and 18 us on a 200 x 300 map (r = 4), so that the count
+// decides there too; at equal counts the longer loop reloads the queries less often (104 x 208, D = 512: 158 us in groups of
+// eight, 161 in groups of four).  Before and after, 200 x 300 map, r = 4, us: D = 96 109 -> 98 (four chunks, three),
+// 160 146 -> 121, 192 145 -> 129, 320 321 -> 225, 384 331 -> 263, 640 468 -> 388 (all of them eight before).
 hipError_t launch_block(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s) {
-    static const BlockLauncher c4[CORR_R] = {launch_block_r1_c4, launch_block_r2_c4, launch_block_r3_c4, launch_block_r4_c4};
-    static const BlockLauncher c8[CORR_R] = {launch_block_r1_c8, launch_block_r2_c8, launch_block_r3_c8, launch_block_r4_c8};
-    return (p->D <= 4 * CORR_CHUNK ? c4 : c8)[q.r - 1](p, ws, q, s);
+#define CORR_RADII(NC) {launch_block_r1_c##NC, launch_block_r2_c##NC, launch_block_r3_c##NC, launch_block_r4_c##NC}
+    static const BlockLauncher c3[CORR_R] = CORR_RADII(3), c4[CORR_R] = CORR_RADII(4), c5[CORR_R] = CORR_RADII(5),
+                               c6[CORR_R] = CORR_RADII(6), c8[CORR_R] = CORR_RADII(8);
+#undef CORR_RADII
+    const int nc = p->D / CORR_CHUNK;
+    const BlockLauncher* of;
+    if (nc <= 8) {
+        of = nc <= 3 ? c3 : nc == 4 ? c4 : nc == 5 ? c5 : nc == 6 ? c6 : c8;
+    } else {
+        const int n4 = (nc + 3) / 4 * 4, n5 = (nc + 4) / 5 * 5, n8 = (nc + 7) / 8 * 8;
+        of = n8 <= n5 && n8 <= n4 ? c8 : n5 <= n4 ? c5 : c4;
+    }
+    return of[q.r - 1](p, ws, q, s);
 }
 
 // planning pass + block kernel on workspace `ws`

@@ -185,16 +185,15 @@ hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s
 hipError_t launch_fill_i32(int* dst, int value, size_t n, hipStream_t s);
 hipError_t launch_binning(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
 hipError_t launch_bin_stats(const corr_pyramid* p, const BinWs& ws, int r, hipStream_t s);
-// one instantiation of block.hip per lookup radius and number of channel chunks in its loop (_c4: D <= 128)
+// one instantiation of block.hip per lookup radius and number of 32-channel chunks in its loop; 4, 5 and 8 also run D in groups
 typedef hipError_t (*BlockLauncher)(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r1_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r2_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r3_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r4_c4(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r1_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r2_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r3_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
-hipError_t launch_block_r4_c8(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+#define CORR_DECLARE_BLOCK(NC)                                                                                             \
+    hipError_t launch_block_r1_c##NC(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);          \
+    hipError_t launch_block_r2_c##NC(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);          \
+    hipError_t launch_block_r3_c##NC(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);          \
+    hipError_t launch_block_r4_c##NC(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s);
+CORR_DECLARE_BLOCK(3) CORR_DECLARE_BLOCK(4) CORR_DECLARE_BLOCK(5) CORR_DECLARE_BLOCK(6) CORR_DECLARE_BLOCK(8)
+#undef CORR_DECLARE_BLOCK
 hipError_t launch_ondemand(const corr_pyramid* p, const LookupArgs& q, hipStream_t s);
 // gradient of the lookup (backward.hip): `ws` holds corr_backward_workspace_floats() floats
 size_t corr_backward_workspace_floats(int B, int H, int W, int D, int L);      // the gradient arrays

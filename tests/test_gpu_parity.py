@@ -405,11 +405,11 @@ def test_full_volume_tiles_and_remainders(B, H, W, D, L, r, nhwc):
     pyr.destroy()
 
 
-@pytest.mark.parametrize("D", [32, 128, 160])
+@pytest.mark.parametrize("D", [32, 96, 128, 160, 192, 224, 288, 352, 512, 544])
 @pytest.mark.parametrize("r", [1, 2, 3, 4])
 def test_block_channel_loops(D, r):
-    """Both sides of the line between the block kernel's loops over four and eight channel chunks, and a loop of one, at
-    every radius and in both precisions."""
+    """Every length of the block kernel's channel loop, full and not, alone and in groups, at every radius and in both
+    precisions."""
     b = _binding()
     f1, f2, c = synth.small_case(60 + D + r, 1, 19, 37, D, flow_range=8.0)
     ref = oracle.lookup(f1, f2, c, L=4, r=r)
