@@ -83,6 +83,38 @@ __global__ __launch_bounds__(256, 2) void vol_gemm_kernel(const float* __restric
                 for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa3[i][PA[m]], fb3[j][PB[m]], acc[i][j], 0, 0, 0);
     }
+    // An infinity, a NaN or a value beyond bf16's range has no three parts (its remainder is infinity - infinity): what is not finite
+    // here is taken from fp32 instructions instead, four channels of a row per lane and 16 a step.
+    float none = 0.f;                                    // NaN if any sum is not finite
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) none = fmaf(acc[i][j][e], 0.f, none);
+    if (__any(none != 0.f)) {
+        f32x4 plain[4][2] = {};
+        for (int k0 = 0; k0 < D; k0 += 16) {
+            f32x4 xa[4], xb[2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) xa[i] = *reinterpret_cast<const f32x4*>(A + (size_t)min(p0 + wp + 16 * i + lr, N - 1) * D + k0 + 4 * lg);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) xb[j] = *reinterpret_cast<const f32x4*>(Bm + (size_t)min(q0 + wq + 16 * j + lr, N - 1) * D + k0 + 4 * lg);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) plain[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[i][c], xb[j][c], plain[i][j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (!(fabsf(acc[i][j][e]) < INFINITY)) acc[i][j][e] = plain[i][j][e];
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
