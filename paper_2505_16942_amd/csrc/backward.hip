@@ -35,6 +35,21 @@ struct BwdArgs {
     float scale;
 };
 
+// Weight of footprint point (pu, pv): of the taps (i, j) = (pu - du, pv - dv), du, dv in {0, 1}, with their corner weights.  Tap
+// (i, j), i the x offset, is taps[(i * K + j) * stride].
+__device__ __forceinline__ float footprint_weight(const float* taps, int stride, int K, int pu, int pv, float fx, float fy) {
+    float g = 0.f;
+#pragma unroll
+    for (int dv = 0; dv < 2; ++dv)
+#pragma unroll
+        for (int du = 0; du < 2; ++du) {
+            const int i = pu - du, j = pv - dv;
+            if (i >= 0 && i < K && j >= 0 && j < K)
+                g += taps[(size_t)(i * K + j) * stride] * (du ? fx : 1.f - fx) * (dv ? fy : 1.f - fy);
+        }
+    return g;
+}
+
 __global__ __launch_bounds__(64 * BQ) void bwd_query_kernel(BwdArgs a) {
     __shared__ float s_taps[BQ][MAXK * MAXK];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -70,17 +85,7 @@ __global__ __launch_bounds__(64 * BQ) void bwd_query_kernel(BwdArgs a) {
             for (int pu = 0; pu <= K; ++pu) {
                 const int u = x0 + pu;
                 if (u < 0 || u >= Wl) continue;
-                // taps (i, j) = (pu - du, pv - dv), du, dv in {0, 1}; tap channel = i*K + j, i the x offset
-                float g = 0.f;
-#pragma unroll
-                for (int dv = 0; dv < 2; ++dv)
-#pragma unroll
-                    for (int du = 0; du < 2; ++du) {
-                        const int i = pu - du, j = pv - dv;
-                        if (i >= 0 && i < K && j >= 0 && j < K)
-                            g += s_taps[wave][i * K + j] * (du ? fx : 1.f - fx) * (dv ? fy : 1.f - fy);
-                    }
-                g *= a.scale;
+                const float g = footprint_weight(s_taps[wave], 1, K, pu, pv, fx, fy) * a.scale;
                 const size_t row = ((size_t)b * Hl * Wl + (size_t)v * Wl + u) * a.D;
                 const float* f2p = a.f2[l] + row;
                 float* dp = a.d_f2[l] + row;
@@ -619,12 +624,93 @@ struct GatherOne {
     size_t part_stride;
 };
 struct GatherArgs {
-    GatherOne out[2];           // blockIdx.z = which * B + batch item
+    GatherOne out[2];           // blockIdx.z = which * B + batch item; 0: d_fmap1, 1: d_fmap2
     int Hl[CORR_MAX_L], Wl[CORR_MAX_L];
     int B, D, W, HW;
+    // for what the item form left not finite (set for that form only)
+    bool mend;
+    int r, L;
+    float scale;
+    CellGrid grid;
+    const float *f1, *f2[CORR_MAX_L], *coords, *d_out;
+    const int *bin_off, *n_items, *perm;
+    const float2* sorted_c;
 };
+// An infinity, a NaN or a value beyond bf16's range (3.39e38) has no three bf16 parts: the item form's contractions make NaN of it,
+// and 0 * NaN carries that over the whole window, into sums whose footprints hold nothing of the kind.  So what comes out not finite is
+// summed again here over the footprints alone, in fp32, by the wave that found it.  Where there is nothing to mend that costs the
+// check (the call on 270 x 480, D = 256: 1.23 ms with and without); detected in the item kernel instead, by its operands or by
+// its sums, it cost that kernel 2 to 10 us a call.
+//
+// A wave's 64 lanes are 16 channels x 4 rows at a time.  s += weight * row for the lanes' rows (`hit`: the lane has one), row numbers
+// and weights one per lane
+__device__ __forceinline__ float add_rows(float s, const float* rows, int D, int ch, bool hit, float weight, int row) {
+    if (!__any(hit)) return s;
+    const float* from = rows + min(ch, D - 1);
+    row = hit ? row : -1;
+#pragma unroll
+    for (int i = 0; i < 64; i += 4) {                      // all loads in flight
+        const int lane = i + ((threadIdx.x & 63) >> 4), r = __shfl(row, lane);
+        const float w = __shfl(weight, lane), v = from[(size_t)max(r, 0) * D];
+        s = r >= 0 ? fmaf(w, v, s) : s;
+    }
+    return s;
+}
+__device__ __forceinline__ float add_groups(float s) {
+    s += __shfl_xor(s, 16);
+    return s + __shfl_xor(s, 32);
+}
+// d_fmap1 of query p, channel ch
+__device__ __forceinline__ float query_again(const GatherArgs& g, int b, int p, int ch) {
+    const int lane = threadIdx.x & 63, K = 2 * g.r + 1, points = (K + 1) * (K + 1);
+    const float cx = g.coords[((size_t)b * 2 + 0) * g.HW + p], cy = g.coords[((size_t)b * 2 + 1) * g.HW + p];
+    float s = 0.f;
+    if (!(fabsf(cx) <= CORR_COORD_LIMIT && fabsf(cy) <= CORR_COORD_LIMIT)) return s;     // uniform
+    for (int l = 0; l < g.L; ++l) {
+        const float inv = __uint_as_float((uint32_t)(127 - l) << 23);
+        const float cxl = cx * inv, cyl = cy * inv, flx = floorf(cxl), fly = floorf(cyl);
+        const float* taps = g.d_out + (size_t)(b * g.L + l) * K * K * g.HW + p;
+        for (int i0 = 0; i0 < points; i0 += 64) {
+            const int i = i0 + lane, pu = i / (K + 1), pv = i - pu * (K + 1), x = (int)flx - g.r + pu, y = (int)fly - g.r + pv;
+            const bool hit = i < points && x >= 0 && x < g.Wl[l] && y >= 0 && y < g.Hl[l];
+            const float w = hit ? footprint_weight(taps, g.HW, K, pu, pv, cxl - flx, cyl - fly) * g.scale : 0.f;
+            s = add_rows(s, g.f2[l], g.D, ch, hit, w, hit ? (b * g.Hl[l] + y) * g.Wl[l] + x : 0);
+        }
+    }
+    return add_groups(s);
+}
+// gradient of point (x, y) of level l, channel ch: over the queries whose footprints hold it, from the cells their targets can lie in
+__device__ __forceinline__ float point_again(const GatherArgs& g, int b, int l, int y, int x, int ch) {
+    const int lane = threadIdx.x & 63, K = 2 * g.r + 1;
+    const float inv = __uint_as_float((uint32_t)(127 - l) << 23);
+    // floor(target) >> l is in x - r - 1 .. x + r
+    const int u0 = max(((x - g.r - 1) * (1 << l)) >> CORR_LOG_CX, g.grid.u_min) - g.grid.u_min;
+    const int v0 = max(((y - g.r - 1) * (1 << l)) >> CORR_LOG_CY, g.grid.v_min) - g.grid.v_min;
+    const int u1 = min((((x + g.r + 1) * (1 << l) - 1) >> CORR_LOG_CX) - g.grid.u_min, g.grid.nbx - 1);
+    const int v1 = min((((y + g.r + 1) * (1 << l) - 1) >> CORR_LOG_CY) - g.grid.v_min, g.grid.nby - 1);
+    const int last = g.B * CORR_TILE_CELLS * g.grid.tnx * g.grid.tny - 1;
+    const float* taps = g.d_out + (size_t)(b * g.L + l) * K * K * g.HW;
+    float s = 0.f;
+    for (int v = v0; v <= v1; ++v)
+        for (int u = u0; u <= u1; ++u) {
+            const int cell = corr_cell_id(g.grid, b, u, v);
+            const int begin = g.bin_off[cell * CORR_SUB], end = cell < last ? g.bin_off[(cell + 1) * CORR_SUB] : g.n_items[1];
+            for (int i0 = begin; i0 < end; i0 += 64) {
+                const int i = min(i0 + lane, end - 1);
+                const float2 c = g.sorted_c[i];
+                const float cxl = c.x * inv, cyl = c.y * inv, flx = floorf(cxl), fly = floorf(cyl);
+                const int pu = x - ((int)flx - g.r), pv = y - ((int)fly - g.r);
+                const bool hit = i0 + lane < end && (unsigned)pu <= (unsigned)K && (unsigned)pv <= (unsigned)K;
+                const int q = g.perm[i];                           // of the whole batch
+                const float w = hit ? footprint_weight(taps + (q - b * g.HW), g.HW, K, pu, pv, cxl - flx, cyl - fly) * g.scale : 0.f;
+                s = add_rows(s, g.f1, g.D, ch, hit, w, q);
+            }
+            if (__all(s != s || ch >= g.D)) return s;              // NaN for good
+        }
+    return add_groups(s);
+}
 constexpr int TP = 64, TC = 64;
-__global__ __launch_bounds__(256) void bwd_gather_nchw_kernel(GatherArgs g) {
+__global__ __launch_bounds__(256, 8) void bwd_gather_nchw_kernel(GatherArgs g) {
     __shared__ float tile[TC][TP + 1];
     const int which = (int)blockIdx.z / g.B, b = (int)blockIdx.z - which * g.B;
     const GatherOne& o = g.out[which];
@@ -656,10 +742,52 @@ __global__ __launch_bounds__(256) void bwd_gather_nchw_kernel(GatherArgs g) {
         }
     }
     __syncthreads();
+    float sum = 0.f;                                       // not finite if any element is not
 #pragma unroll
     for (int k = 0; k < TP * TC / 256; ++k) {
         const int idx = threadIdx.x + 256 * k, px = idx & (TP - 1), chn = idx / TP;
-        if (d0 + chn < g.D && p0 + px < g.HW) o.dst[((size_t)b * g.D + d0 + chn) * g.HW + p0 + px] = tile[chn][px];
+        if (d0 + chn < g.D && p0 + px < g.HW) {
+            const float v = tile[chn][px];
+            o.dst[((size_t)b * g.D + d0 + chn) * g.HW + p0 + px] = v;
+            sum += v;
+        }
+    }
+    if (!g.mend || !__any(!(fabsf(sum) < INFINITY))) return;
+    // the wave's channels of the tile: d0 + wave + 4 * i
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, chn = wave + 4 * (lane & 15), ch = d0 + chn;
+    bool spoiled = false;
+    for (int i = 0; i < TC / 4; ++i)
+        spoiled |= p0 + lane < g.HW && d0 + wave + 4 * i < g.D && !(fabsf(tile[wave + 4 * i][lane]) < INFINITY);
+    const uint64_t pixels = __ballot(spoiled);
+    auto write = [&](int p, float v) {                     // what was finite stays
+        if (lane < 16 && ch < g.D && !(fabsf(tile[chn][p - p0]) < INFINITY)) o.dst[((size_t)b * g.D + ch) * g.HW + p] = v;
+    };
+    if (which == 0) {
+        for (uint64_t left = pixels; left; left &= left - 1) {
+            const int p = p0 + __builtin_ctzll(left);
+            write(p, query_again(g, b, p, ch));
+        }
+        return;
+    }
+    // the levels' gradients first, in place (a wave of another tile that needs the same point writes the same value), then the fold again
+    for (int l = 0; l < o.L; ++l)
+        for (uint64_t left = pixels; left; left &= left - 1) {
+            const int p = p0 + __builtin_ctzll(left), y = p / g.W >> l, x = p % g.W >> l;
+            if (y >= g.Hl[l] || x >= g.Wl[l]) continue;
+            float* d = const_cast<float*>(o.d[l]) + (((size_t)b * g.Hl[l] + y) * g.Wl[l] + x) * g.D + ch;
+            const bool bad = ch < g.D && !(fabsf(__hip_atomic_load(d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < INFINITY);
+            if (!__any(bad)) continue;
+            const float v = point_again(g, b, l, y, x, ch);
+            if (bad && lane < 16) __hip_atomic_store(d, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __threadfence_block();                         // the next pixel may have the same point
+        }
+    for (uint64_t left = pixels; left; left &= left - 1) {
+        const int p = p0 + __builtin_ctzll(left), y = p / g.W, x = p % g.W;
+        float v = 0.f;
+        for (int l = o.L - 1; l >= 0; --l)
+            if ((y >> l) < g.Hl[l] && (x >> l) < g.Wl[l] && ch < g.D)
+                v = __hip_atomic_load(o.d[l] + (((size_t)b * g.Hl[l] + (y >> l)) * g.Wl[l] + (x >> l)) * g.D + ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 0.25f * v;
+        write(p, v);
     }
 }
 
@@ -717,6 +845,7 @@ hipError_t launch_backward(const corr_pyramid* p, const float* coords, const flo
     const float scale = 1.0f / sqrtf((float)p->D);
     const long long BN = (long long)p->B * HW;
     hipError_t e;
+    GatherArgs ga{};
     if (form == CORR_BACKWARD_ITEMS) {
         // Everything accumulates or keeps its zero; in the planning workspace the bin counters, the item counters and
         // the item kernel's queues (kept in the statistics slots) start at zero, the rest is written before it is
@@ -751,6 +880,8 @@ hipError_t launch_backward(const corr_pyramid* p, const float* coords, const flo
             a.f2[l] = l < p->L ? p->f2_nhwc[l] : nullptr; a.d_f2[l] = d_f2[l];
             a.Hl[l] = p->Hl[l]; a.Wl[l] = p->Wl[l];
         }
+        ga.mend = true;
+        ga.bin_off = bws.bin_off; ga.n_items = bws.n_items; ga.perm = bws.perm; ga.sorted_c = bws.sorted_c;
         hipLaunchKernelGGL(bwd_item_kernel, dim3(CORR_NUM_CU), dim3(NTI), ITEM_LDS, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
@@ -767,7 +898,6 @@ hipError_t launch_backward(const corr_pyramid* p, const float* coords, const flo
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // both gradients to NCHW in one launch: d_fmap1 (a small input's per-level shares summed), d_fmap2 (levels folded)
-    GatherArgs ga;
     for (int l = 0; l < CORR_MAX_L; ++l) {
         ga.Hl[l] = p->Hl[l]; ga.Wl[l] = p->Wl[l];
         ga.out[0].d[l] = nullptr; ga.out[1].d[l] = d_f2[l];
@@ -776,6 +906,8 @@ hipError_t launch_backward(const corr_pyramid* p, const float* coords, const flo
     ga.out[0].parts = parts; ga.out[0].part_stride = (size_t)p->B * HW * p->D;
     ga.out[1].dst = d_fmap2; ga.out[1].L = p->L; ga.out[1].parts = 1; ga.out[1].part_stride = 0;
     ga.B = p->B; ga.D = p->D; ga.W = p->W; ga.HW = HW;
+    ga.r = r; ga.L = p->L; ga.scale = scale; ga.grid = p->grid; ga.f1 = p->f1_nhwc; ga.coords = coords; ga.d_out = d_out;
+    for (int l = 0; l < CORR_MAX_L; ++l) ga.f2[l] = l < p->L ? p->f2_nhwc[l] : nullptr;
     hipLaunchKernelGGL(bwd_gather_nchw_kernel, dim3((HW + TP - 1) / TP, (p->D + TC - 1) / TC, 2 * p->B), dim3(256), 0, s, ga);
     return hipGetLastError();
 }

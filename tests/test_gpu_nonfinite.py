@@ -53,3 +53,39 @@ def test_full_volume():
     # level 0: the deeper levels pool the volume, where infinities of both signs meet, and not the features
     _check(flat(got)[:, :81], flat(ref)[:, :81], 1e-5, "full volume, level 0", axis=2)
     pyr.destroy()
+
+
+# item form with an item's levels in workgroups of their own, in one; one wave per query
+@pytest.mark.parametrize("items,split", [(True, -1), (True, 0), (False, -1)])
+# a map of one binning workgroup's queries and one of more, with two batch items
+@pytest.mark.parametrize("B,H,W,D,r", [(1, 26, 44, 64, 4), (1, 26, 44, 288, 4), (1, 26, 44, 256, 3), (2, 38, 62, 96, 2)])
+@pytest.mark.parametrize("where", ["features", "d_out"])
+def test_gradient(where, B, H, W, D, r, items, split):
+    b = _binding()
+    dev = torch.device("cuda:0")
+    L, K, last = 4, 2 * r + 1, B - 1
+    f1, f2, c = synth.small_case(50 + D + r, B, H, W, D, flow_range=3.0)
+    d_out = np.random.default_rng(D).standard_normal((B, L * K * K, H, W)).astype(np.float32)
+    c[last, :, 7, 8] = (9.0, 6.0)                        # weights of zero
+    if where == "features":
+        f1[last, 3, 4, 5], f1[last, 20, 11, 30], f1[last, 31, 7, 8] = INF, NAN, -INF
+        f2[last, 5, 9, 9], f2[last, 17, 2, 40], f2[last, 30, 25, 20] = -INF, NAN, INF
+        f1[last, 9, 18, 3] = f2[last, 11, 20, 30] = HUGE
+    else:
+        d_out[last, 0, 5, 6], d_out[last, K * K + 3, 14, 33], d_out[last, L * K * K - 1, 7, 8] = INF, NAN, -INF
+    want1, want2 = oracle.backward(f1, f2, c, d_out, L=L, r=r)
+    t1, t2, tc, tg = (torch.from_numpy(a).to(dev) for a in (f1, f2, c, d_out))
+    pyr = b.corr_pyramid_build(t1, t2, L=L, reps=b.CORR_REP_F32)
+    prev = b.corr_debug_set_backward_form(b.CORR_BACKWARD_ITEMS if items else b.CORR_BACKWARD_QUERIES)
+    prev_split = b.corr_debug_set_level_split(split)
+    try:
+        print("gradient", where, B, H, W, D, r, items, split, flush=True)
+        g1, g2 = b.corr_sample_backward(pyr, tc, tg, r=r)
+        torch.cuda.synchronize()
+    finally:
+        b.corr_debug_set_backward_form(prev)
+        b.corr_debug_set_level_split(prev_split)
+    # a tap gradient's infinity may come out as NaN: the footprint's weights are interpolated
+    for got, want, name in ((g1, want1, "d_fmap1"), (g2, want2, "d_fmap2")):
+        _check(got, want, 1e-4, "%s, %s, D=%d r=%d" % (name, where, D, r), kinds=where == "features")
+    pyr.destroy()
