@@ -149,9 +149,23 @@ def _dev_f32(t: torch.Tensor, name: str) -> int:
     return t.data_ptr()
 
 
-def _stream() -> int:
-    # the current device's current stream, as torch.cuda.current_stream().cuda_stream gives it, without the Stream object (3 us)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _stream_handle():
+    """A function that gives the current device's current stream.  torch's own lookup of the handle saves the Stream object that
+    current_stream() makes (3 us); it is not part of torch's public interface, so another torch may be without it."""
+    raw, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_stream = _stream_handle()
+
+
+def _new_out(shape, coords: torch.Tensor) -> torch.Tensor:
+    """A plain tensor whatever coords' class (new_empty, the shorter call, keeps a subclass)."""
+    if type(coords) is torch.Tensor:
+        return coords.new_empty(shape)
+    return torch.empty(shape, dtype=torch.float32, device=coords.device)
 
 
 def _stream_or_null():
@@ -213,7 +227,7 @@ def corr_sample(fmap1, pyramid: Pyramid, coords: torch.Tensor, r: int = 4,
     K = 2 * r + 1
     shape = (B, H, W, L * K * K) if layout == CORR_OUT_NHWC else (B, L * K * K, H, W)
     if out is None:
-        out = coords.new_empty(shape)
+        out = _new_out(shape, coords)
         po = out.data_ptr()
     elif tuple(out.shape) != shape:
         raise ValueError("out has the wrong shape")
@@ -238,7 +252,7 @@ def corr_sample_static(fmap1, pyramid: Pyramid, coords: torch.Tensor, r: int = 4
     K = 2 * r + 1
     shape = (B, L * K * K, H, W)
     if out is None:
-        out = coords.new_empty(shape)
+        out = _new_out(shape, coords)
         po = out.data_ptr()
     elif tuple(out.shape) != shape:
         raise ValueError("out has the wrong shape")

@@ -129,3 +129,27 @@ def test_binning_workspace_against_the_rule(case):
     st = b.corr_last_block_stats(pyr, 4)
     assert st["items"] == len(items)
     pyr.destroy()
+
+
+def test_outputs_are_plain_tensors_on_the_current_stream(monkeypatch):
+    """A tensor subclass as coords gives a plain tensor back; the stream's handle is current_stream()'s, also where torch lacks
+    the shorter way to it."""
+    class Own(torch.Tensor):
+        pass
+
+    b = _binding()
+    dev = torch.device("cuda:0")
+    f1, f2, c = synth.small_case(3, 1, 16, 24, 32)
+    t1, t2, tc = (torch.from_numpy(a).to(dev) for a in (f1, f2, c))
+    pyr = b.corr_pyramid_build(t1, t2, L=2)
+    want = b.corr_sample(t1, pyr, tc)
+    for call in (b.corr_sample, b.corr_sample_static):
+        got = call(t1, pyr, tc.as_subclass(Own))
+        assert type(got) is torch.Tensor and torch.equal(got, want)
+    side = torch.cuda.Stream()
+    assert b._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert b._stream() == side.cuda_stream
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+        assert b._stream_handle()() == side.cuda_stream
+    pyr.destroy()
