@@ -417,3 +417,27 @@ def test_block_channel_loops(D, r):
     _check(got, ref, FP32_TOL, "block D=%d r=%d" % (D, r))
     got, _ = _run(f1, f2, c, 4, r, b.CORR_MODE_BLOCK, prec=b.CORR_PREC_BF16, reps=b.CORR_REP_BF16)
     _check(got, ref, None, "block bf16 D=%d r=%d" % (D, r), bound=bf16_bound(f1, f2, ref))
+
+
+@pytest.mark.parametrize("D", [32, 128, 160, 192, 224, 352, 480, 512])
+def test_block_channel_loops_channels_last(D):
+    """Channels-last kernels of every loop length and group size, at every radius: the same values as NCHW, bit for bit, in both
+    precisions; the reduced one also reads the hi parts of a split pyramid."""
+    b = _binding()
+    dev = torch.device("cuda:0")
+    f1, f2, c = synth.small_case(61 + D, 1, 19, 37, D, flow_range=8.0)
+    t1, t2, tc = (torch.from_numpy(a).to(dev) for a in (f1, f2, c))
+    split = b.corr_pyramid_build(t1, t2, L=4, reps=b.CORR_REP_SPLIT)
+    hi = b.corr_pyramid_build(t1, t2, L=4, reps=b.CORR_REP_BF16)
+    for r in (1, 2, 3, 4):
+        for pyr, prec in ((split, b.CORR_PREC_BF16X3), (split, b.CORR_PREC_BF16), (hi, b.CORR_PREC_BF16)):
+            out = torch.full((1, 19, 37, 4 * (2 * r + 1) ** 2), float("nan"), device=dev)
+            b.corr_sample(t1, pyr, tc, r=r, prec=prec, layout=b.CORR_OUT_NHWC, out=out)
+            want = b.corr_sample(t1, pyr, tc, r=r, prec=prec)
+            assert torch.equal(out.permute(0, 3, 1, 2), want), (D, r, prec)
+            if pyr is split and prec == b.CORR_PREC_BF16:
+                of_split = want
+            elif pyr is hi:
+                assert torch.equal(of_split, want), (D, r)
+    split.destroy()
+    hi.destroy()
