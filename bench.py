@@ -62,21 +62,23 @@ def bench_backward(args, cb, synth, torch, np) -> int:
     # algorithmic HBM bytes: d_out, fmap1 and every pyramid pixel (fp32) read once, both gradients written once
     bytes_alg = B * (taps // B * 4 + N * D * 4 + npyr * D * 4 + N * 8 + 2 * N * D * 4)
     gbs = bytes_alg / dt / 1e9
-    # the item form's two dense contractions: every query against every point of its cell's window, per level
+    flops_footprint = 4.0 * B * N * L * (K + 1) ** 2 * D       # both gradients on every query's footprints: what the call is for
+    # every query against every point of its cell's window; the item kernel leaves out the (16 queries, 16 or 32 points) blocks
+    # that no footprint reaches, so what it executes lies between the two
     win = sum((max(16 >> l, 1) + K) * (max(8 >> l, 1) + K) for l in range(L))
-    flops_dense = 4.0 * B * N * win * D
-    flops_footprint = 4.0 * B * N * L * (K + 1) ** 2 * D       # what the gradient needs at the least
-    tfs = flops_dense / dt / 1e12
+    flops_window = 4.0 * B * N * win * D
+    tfs = flops_footprint / dt / 1e12
     if form == cb.CORR_BACKWARD_ITEMS:
         roof = {"bound": "mfma", "achieved": round(tfs, 2), "peak": PEAK_FP32_AS_BF16_TFS, "unit": "TFLOP/s",
                 "frac": round(tfs / PEAK_FP32_AS_BF16_TFS, 4), "traffic": None,
                 "kernel": "bwd_item_kernel (per work item and level: G^T x f2 rows and G x f1 rows as six bf16 MFMA products, "
                           "window rows of d f2 out through float atomics); the time is the whole call's",
-                "flops_per_call": flops_dense, "footprint_flops_per_call": flops_footprint,
+                "flops_per_call": flops_footprint, "window_flops_per_call": flops_window,
                 "hbm": {"achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4),
                         "algorithmic_bytes_per_call": bytes_alg},
-                "note": "flops = 4 * queries * window points of the cell (%d over the levels) * D, unpadded; "
-                        "peak = dense bf16 MFMA / 6 (fp32 precision takes six bf16 products)" % win}
+                "note": "flops = 4 * queries * footprint points (%d over the levels) * D, what the gradient needs, not what the "
+                        "kernel multiplies (window: %d points); "
+                        "peak = dense bf16 MFMA / 6 (fp32 precision takes six bf16 products)" % (L * (K + 1) ** 2, win)}
     else:
         atomics = float(B * N * L * (K + 1) ** 2 * D)
         roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
@@ -428,8 +430,7 @@ def main() -> int:
             cb.corr_sample_backward(pg, ucs[0], d_out, r=r, d_fmap1=q1, d_fmap2=q2, workspace=wsb)
         torch.cuda.synchronize()
         dtb = (time.perf_counter() - tb) / args.steps
-        win = sum((max(16 >> l, 1) + K) * (max(8 >> l, 1) + K) for l in range(L4))
-        tfs = 4.0 * B4 * H4 * W4 * win * c4["D"] / dtb / 1e12
+        tfs = 4.0 * B4 * H4 * W4 * L4 * (K + 1) ** 2 * c4["D"] / dtb / 1e12      # on the footprints
         result["backward_at_4k"] = {"workload": "4k, one corr_sample_backward per step (fp32, work items on the matrix cores)",
                                     "value": B4 * H4 * W4 * L4 * K * K / dtb, "unit": "tap gradients/s",
                                     "ms_per_step": dtb * 1e3, "steps": args.steps,
