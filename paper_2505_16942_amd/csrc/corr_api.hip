@@ -134,10 +134,13 @@ std::atomic<int> g_backward_form{CORR_BACKWARD_ITEMS};
 
 // The block kernel's channel loop has a fixed length; chunks past the last one are loaded and multiplied as zeros, so the
 // length with the fewest chunks in all is taken.  Up to 256 channels that is the shortest loop that holds D.  Beyond, D runs
-// in groups of 4, 5 or 8 chunks, whose times per chunk are 18, 16 and 18 us on a 200 x 300 map (r = 4), so that the count
-// decides there too; at equal counts the longer loop reloads the queries less often (104 x 208, D = 512: 158 us in groups of
-// eight, 161 in groups of four).  Before and after, 200 x 300 map, r = 4, us: D = 96 109 -> 98 (four chunks, three),
-// 160 146 -> 121, 192 145 -> 129, 320 321 -> 225, 384 331 -> 263, 640 468 -> 388 (all of them eight before).
+// in groups of 4, 5 or 8 chunks.  A chunk more costs about the same in all three (17.0, 16.5 and 17.4 us on a 200 x 300 map, r = 4,
+// bf16x3, D = 288 .. 1024), so that the count decides there too: groups of 4 / 5 / 8, same map, us: D = 352 254 / 298 / 322, 416
+// 319 / 301 / 328, 640 392 / 386 / 466, 896 529 / 550 / 606, 960 593 / 554 / 616; on 46 x 62, 104 x 208 and 270 x 480 maps the same
+// one is fastest.  Where 4 and 8 have equal counts (D = 512, 672 .. 768, 1024) 8 is taken for both precisions.  In bf16 mode it is the
+// faster one (D = 512 211 us against 223, 1024 365 against 393); in bf16x3 groups of 4 would be faster by 3 to 5 % on 46 x 62,
+// 200 x 300 (D = 512 325 against 337, 1024 598 against 615) and 270 x 480 maps, slower by 1 % on 104 x 208.  All eight before, 200 x 300
+// map, r = 4, us: D = 96 109 -> 98 (four chunks, three), 160 146 -> 121, 192 145 -> 129, 320 321 -> 225, 384 331 -> 263, 640 468 -> 388.
 hipError_t launch_block(const corr_pyramid* p, const BinWs& ws, const LookupArgs& q, hipStream_t s) {
 #define CORR_RADII(NC) {launch_block_r1_c##NC, launch_block_r2_c##NC, launch_block_r3_c##NC, launch_block_r4_c##NC}
     static const BlockLauncher c3[CORR_R] = CORR_RADII(3), c4[CORR_R] = CORR_RADII(4), c5[CORR_R] = CORR_RADII(5),

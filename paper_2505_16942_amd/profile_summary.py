@@ -81,7 +81,7 @@ def cmd_stats(args) -> int:
     print("| kernel | grid (threads) | calls | mean us | min us | max us | total ms | share |")
     print("|---|---|---|---|---|---|---|---|")
     for (name, grid), v in sorted(rows.items(), key=lambda kv: -sum(kv[1])):
-        if sum(v) / total < 0.002 and not any(w in name for w in ("corr", "block", "bin", "bwd", "fill_i32")):
+        if sum(v) / total < 0.002 and not any(w in name for w in ("corr", "block", "bin", "bwd", "fill_i32", "vol_")):
             continue
         print("| %s | %d | %d | %.1f | %.1f | %.1f | %.3f | %.1f %% |" % (
             _short(name), grid, len(v), sum(v) / len(v), min(v), max(v), sum(v) / 1e3, 100.0 * sum(v) / total))
