@@ -20,7 +20,7 @@
 //             consecutive lanes); the workgroup that finishes last also runs
 //   scan    : cell and bin offsets, the item list
 //   scatter : queries, and their coordinates, sorted by bin.
-// Small inputs run all three steps in one workgroup.
+// Small inputs run all three steps in one workgroup, on counters in LDS.
 #include "corr_internal.h"
 
 namespace {
@@ -30,7 +30,11 @@ constexpr int SCAN_T = 1024;          // cells per tile of the scan; threads of 
 constexpr int COUNT_T = 1024;         // threads per workgroup of the count kernel
 constexpr int SCAN_CPT = 1;           // cells per thread and tile when its last workgroup scans (2 was no faster, 4 costs
                                       // the kernel its two workgroups per CU)
-constexpr int SMALL_MAX_Q = 2;        // queries per thread of the one-workgroup path
+// The one-workgroup path: queries per thread, and bins, whose counters lie in LDS.  A lookup on one 46 x 62 map (2852 queries) takes 32.5 us this
+// way and 35.6 with the count and scatter launches, 40 x 90 (3600) 31.0 and 32.4; with eight queries a thread 2 x 46 x 62 (5704) gains
+// nothing and 56 x 128 (7168) goes from 43.7 to 46.3.
+constexpr int SMALL_MAX_Q = 4;
+constexpr int SMALL_MAX_BINS = 12288;
 
 struct BinArgs {
     const float* coords;   // [B][2][H*W]
@@ -40,9 +44,8 @@ struct BinArgs {
 };
 
 // bin of query (b, p), or -1 when it is out of range at every level (the block kernel's spare workgroups then write its zeros)
-__device__ __forceinline__ int query_bin(const BinArgs& a, int b, int p) {
-    const float cx = a.coords[((size_t)b * 2 + 0) * a.HW + p];
-    const float cy = a.coords[((size_t)b * 2 + 1) * a.HW + p];
+__device__ __forceinline__ int query_bin(const BinArgs& a, int b, int p, float2 c) {
+    const float cx = c.x, cy = c.y;
     // comparisons are false for NaN, so non-finite coordinates are "not ok"
     const bool finite_ok = (fabsf(cx) <= CORR_COORD_LIMIT) && (fabsf(cy) <= CORR_COORD_LIMIT);
     int bin = -1;
@@ -57,29 +60,18 @@ __device__ __forceinline__ int query_bin(const BinArgs& a, int b, int p) {
 
 // Neighbouring pixels mostly fall in the same bin: one atomic per run of equal bins among
 // consecutive lanes, the rest of the run takes offsets.  Every lane of the wave must call this.
-// In two halves, so that a caller with several queries per thread can have all its atomics in
-// flight before it needs the first result.
-struct RankTicket { int base, head_lane; };
-__device__ __forceinline__ RankTicket take_rank_issue(int* bin_count, int bin) {
+__device__ __forceinline__ int take_rank(int* bin_count, int bin) {
     const int lane = threadIdx.x & 63;
     const int prev = __shfl_up(bin, 1, 64);
     const bool head = (lane == 0) || (bin != prev);
     const unsigned long long heads = __ballot(head);
     const unsigned long long upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-    RankTicket t;
-    t.head_lane = 63 - __clzll((long long)(heads & upto));
+    const int head_lane = 63 - __clzll((long long)(heads & upto));
     const unsigned long long above = heads & ~upto;
     const int next = above ? (__ffsll((long long)above) - 1) : 64;
-    t.base = 0;
-    if (head && bin >= 0) t.base = atomicAdd(&bin_count[bin], next - lane);
-    return t;
-}
-__device__ __forceinline__ int take_rank_finish(const RankTicket& t) {
-    const int lane = threadIdx.x & 63;
-    return __shfl(t.base, t.head_lane, 64) + (lane - t.head_lane);
-}
-__device__ __forceinline__ int take_rank(int* bin_count, int bin) {
-    return take_rank_finish(take_rank_issue(bin_count, bin));
+    int base = 0;
+    if (head && bin >= 0) base = atomicAdd(&bin_count[bin], next - lane);
+    return __shfl(base, head_lane, 64) + (lane - head_lane);
 }
 
 // One workgroup of T threads: exclusive scan of the bin counts (query offsets) and of the per-cell item
@@ -87,8 +79,9 @@ __device__ __forceinline__ int take_rank(int* bin_count, int bin) {
 // clears the counts for the next lookup.  The counts were produced by device-scope atomics of other
 // workgroups, possibly on other XCDs: a caller that runs in the same kernel as those atomics puts an
 // acquire fence in front (this XCD's L2 may hold stale copies of the lines).
-template <int T, int CPT>
-__device__ void scan_cells(const BinWs& ws) {
+// LDS: the counts lie in `counts` (LDS) and the offsets go there too; the counts in the workspace are left alone.
+template <int T, int CPT, bool LDS>
+__device__ void scan_cells(const BinWs& ws, int* counts) {
     static_assert(CORR_SUB == 8, "a cell's counters are two int4");
     __shared__ int s_wc[T / 64], s_wi[T / 64], s_tot[2];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -102,7 +95,7 @@ __device__ void scan_cells(const BinWs& ws) {
         for (int j = 0; j < CPT; ++j) {
             lo[j] = make_int4(0, 0, 0, 0); hi[j] = lo[j];
             if (cell0 + j < ws.ncells) {
-                const int4* pc = reinterpret_cast<const int4*>(ws.bin_count + (size_t)(cell0 + j) * CORR_SUB);
+                const int4* pc = reinterpret_cast<const int4*>(counts + (size_t)(cell0 + j) * CORR_SUB);
                 lo[j] = pc[0]; hi[j] = pc[1];
             }
         }
@@ -151,11 +144,12 @@ __device__ void scan_cells(const BinWs& ws) {
                 const int o1 = coff + lo[j].x, o2 = o1 + lo[j].y, o3 = o2 + lo[j].z, o4 = o3 + lo[j].w;
                 const int o5 = o4 + hi[j].x, o6 = o5 + hi[j].y, o7 = o6 + hi[j].z;
                 int4* po = reinterpret_cast<int4*>(ws.bin_off + (size_t)cell * CORR_SUB);
-                int4* pc = reinterpret_cast<int4*>(ws.bin_count + (size_t)cell * CORR_SUB);
-                po[0] = make_int4(coff, o1, o2, o3);
-                po[1] = make_int4(o4, o5, o6, o7);
-                pc[0] = make_int4(0, 0, 0, 0);                   // ready for the next lookup
-                pc[1] = make_int4(0, 0, 0, 0);
+                int4* pc = reinterpret_cast<int4*>(counts + (size_t)cell * CORR_SUB);
+                const int4 first = make_int4(coff, o1, o2, o3), second = make_int4(o4, o5, o6, o7), none = make_int4(0, 0, 0, 0);
+                po[0] = first;
+                po[1] = second;
+                pc[0] = LDS ? first : none;                      // none: ready for the next lookup
+                pc[1] = LDS ? second : none;
                 coff += csum[j];
             }
         }
@@ -171,7 +165,7 @@ __global__ __launch_bounds__(COUNT_T) void bin_count_kernel(BinArgs a) {
     const bool real = q < BN;                 // lanes past the end stay for the shuffles
     int bin = -1;
     const int b = real ? q / a.HW : 0, p = real ? q - b * a.HW : 0;
-    if (real) bin = query_bin(a, b, p);
+    if (real) bin = query_bin(a, b, p, make_float2(a.coords[((size_t)b * 2 + 0) * a.HW + p], a.coords[((size_t)b * 2 + 1) * a.HW + p]));
     const int rank = take_rank(a.ws.bin_count, bin);
     if (real) { a.ws.q_bin[q] = bin; a.ws.q_rank[q] = rank; }
     // The workgroup that arrives last scans.  Every thread has its atomic's result back before the
@@ -194,7 +188,7 @@ __global__ __launch_bounds__(COUNT_T) void bin_count_kernel(BinArgs a) {
     __syncthreads();
     if (s_last) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");          // once, in one workgroup: drop stale lines, then read normally
-        scan_cells<COUNT_T, SCAN_CPT>(a.ws);
+        scan_cells<COUNT_T, SCAN_CPT, false>(a.ws, a.ws.bin_count);
         __syncthreads();
     }
 }
@@ -211,37 +205,39 @@ __global__ __launch_bounds__(256) void bin_scatter_kernel(BinArgs a) {
     }
 }
 
-// Inputs of up to SCAN_T * SMALL_MAX_Q queries: count, scan and scatter in one workgroup, one launch.
+// Inputs of up to SCAN_T * SMALL_MAX_Q queries and SMALL_MAX_BINS bins: count, scan and scatter in one workgroup, one launch.  Bound by
+// latency: the coordinates' way here, the counters' LDS atomics, the scan and the lists' way out.
 __global__ __launch_bounds__(SCAN_T) void bin_small_kernel(BinArgs a) {
+    __shared__ __align__(16) int counts[SMALL_MAX_BINS];
     const int BN = a.B * a.HW;
+    for (int i = threadIdx.x; i < a.ws.nbins; i += SCAN_T) counts[i] = 0;
     int bin[SMALL_MAX_Q], rank[SMALL_MAX_Q];
-    RankTicket ticket[SMALL_MAX_Q];
+    float2 xy[SMALL_MAX_Q];
 #pragma unroll
     for (int k = 0; k < SMALL_MAX_Q; ++k) {
         const int q = k * SCAN_T + threadIdx.x;
-        bin[k] = -1;
-        const int b = q < BN ? q / a.HW : 0, p = q < BN ? q - b * a.HW : 0;
-        if (q < BN) { bin[k] = query_bin(a, b, p); a.ws.q_bin[q] = bin[k]; }     // the block kernel looks for the queries without a bin
+        bin[k] = -1; rank[k] = 0; xy[k] = make_float2(0.f, 0.f);
+        if (q < BN) {
+            const int b = q / a.HW, p = q - b * a.HW;
+            xy[k] = make_float2(a.coords[((size_t)b * 2 + 0) * a.HW + p], a.coords[((size_t)b * 2 + 1) * a.HW + p]);
+            bin[k] = query_bin(a, b, p, xy[k]);
+            a.ws.q_bin[q] = bin[k];                                   // the block kernel looks for the queries without a bin
+        }
     }
-    // all of a thread's atomics are in flight before the first result is used
+    __syncthreads();                  // every counter is zero
 #pragma unroll
-    for (int k = 0; k < SMALL_MAX_Q; ++k) {
-        ticket[k].base = 0; ticket[k].head_lane = 0;
-        if (k * SCAN_T < BN) ticket[k] = take_rank_issue(a.ws.bin_count, bin[k]);        // uniform condition
-    }
-#pragma unroll
-    for (int k = 0; k < SMALL_MAX_Q; ++k) rank[k] = (k * SCAN_T < BN) ? take_rank_finish(ticket[k]) : 0;
-    __syncthreads();                  // every atomic of this workgroup has returned
-    scan_cells<SCAN_T, 1>(a.ws);
-    __syncthreads();                  // the offsets were written by threads of this workgroup
+    for (int k = 0; k < SMALL_MAX_Q; ++k)
+        if (k * SCAN_T < BN) rank[k] = take_rank(counts, bin[k]);      // uniform condition
+    __syncthreads();                  // every count is whole
+    scan_cells<SCAN_T, 1, true>(a.ws, counts);
+    __syncthreads();                  // every offset is there
 #pragma unroll
     for (int k = 0; k < SMALL_MAX_Q; ++k) {
         const int q = k * SCAN_T + threadIdx.x;
         if (q < BN && bin[k] >= 0) {
-            const int b = q / a.HW, p = q - b * a.HW;
-            const int pos = a.ws.bin_off[bin[k]] + rank[k];
+            const int pos = counts[bin[k]] + rank[k];
             a.ws.perm[pos] = q;
-            a.ws.sorted_c[pos] = make_float2(a.coords[((size_t)b * 2 + 0) * a.HW + p], a.coords[((size_t)b * 2 + 1) * a.HW + p]);
+            a.ws.sorted_c[pos] = xy[k];
         }
     }
 }
@@ -323,7 +319,7 @@ hipError_t launch_binning(const corr_pyramid* p, const BinWs& ws, const LookupAr
     BinArgs a;
     a.coords = q.coords; a.B = p->B; a.HW = HW; a.W = p->W; a.L = p->L; a.r = q.r; a.g = p->grid;
     a.ws = ws;
-    if (BN <= SCAN_T * SMALL_MAX_Q) {
+    if (BN <= SCAN_T * SMALL_MAX_Q && ws.nbins <= SMALL_MAX_BINS) {
         hipLaunchKernelGGL(bin_small_kernel, dim3(1), dim3(SCAN_T), 0, s, a);
         return hipGetLastError();
     }

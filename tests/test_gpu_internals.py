@@ -131,6 +131,13 @@ def test_binning_workspace_against_the_rule(case):
     pyr.destroy()
 
 
+@pytest.mark.parametrize("case", [(1, 31, 66, 4, 9.0), (1, 33, 65, 4, 9.0), (1, 64, 64, 4, 9.0), (1, 17, 241, 3, 9.0),
+                                  (48, 9, 9, 2, 3.0), (49, 9, 9, 2, 3.0)])
+def test_binning_workspace_at_the_edges_of_the_one_workgroup_path(case):
+    """Up to 4096 queries and 12288 bins take one workgroup: 2046, 2145, 4096 and 4097 queries, 12288 and 12544 bins."""
+    test_binning_workspace_against_the_rule(case)
+
+
 def test_outputs_are_plain_tensors_on_the_current_stream(monkeypatch):
     """A tensor subclass as coords gives a plain tensor back; the stream's handle is current_stream()'s, also where torch lacks
     the shorter way to it."""
