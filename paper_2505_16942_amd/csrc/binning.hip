@@ -20,7 +20,7 @@
 //             consecutive lanes); the workgroup that finishes last also runs
 //   scan    : cell and bin offsets, the item list
 //   scatter : queries, and their coordinates, sorted by bin.
-// Small inputs run all three steps in one workgroup, on counters in LDS.
+// Small inputs run all three steps in one workgroup, on counters in LDS where these fit.
 #include "corr_internal.h"
 
 namespace {
@@ -30,11 +30,18 @@ constexpr int SCAN_T = 1024;          // cells per tile of the scan; threads of 
 constexpr int COUNT_T = 1024;         // threads per workgroup of the count kernel
 constexpr int SCAN_CPT = 1;           // cells per thread and tile when its last workgroup scans (2 was no faster, 4 costs
                                       // the kernel its two workgroups per CU)
-// The one-workgroup path: queries per thread, and bins, whose counters lie in LDS.  A lookup on one 46 x 62 map (2852 queries) takes 32.5 us this
-// way and 35.6 with the count and scatter launches, 40 x 90 (3600) 31.0 and 32.4; with eight queries a thread 2 x 46 x 62 (5704) gains
-// nothing and 56 x 128 (7168) goes from 43.7 to 46.3.
+// The one-workgroup path.  Its counters lie in LDS for up to 4096 queries (SMALL_MAX_Q a thread) and 12288 bins (48 KB, within what a kernel may
+// declare without a raised limit).  Inputs of more bins, batches of many small maps, have them in the workspace and take this path up to 2048 queries
+// (SMALL_WS_MAX_Q a thread).  Whole lookups, D = 256, r = 4, smooth flow, us:
+//   one workgroup with LDS / count and scatter launches: 46 x 62 (2852 queries) 29.4 / 32.0, 40 x 90 30.4 / 32.3, 64 x 64 31.6 / 32.8, 12 maps of
+//   18 x 18 (12288 bins) 45.9 / 47.8; eight queries a thread gain nothing: 2 x 46 x 62 (5704) 42.7 / 41.7, 56 x 128 (7168) 45.3 / 42.8;
+//   one workgroup with LDS / with the workspace: 12 maps of 8 x 8 (768 queries, 12288 bins) 20.2 / 21.5;
+//   one workgroup with the workspace / count and scatter launches: 13 maps of 8 x 8 (13312 bins) 21.8 / 25.7, 32 (2048 queries, 32768 bins) 41.5 / 44.0;
+//   four queries a thread: 13 maps of 17 x 17 (3757 queries) 48.2 / 47.5, 20 of 14 x 14 (3920) 52.3 / 51.8.
+// Open: LDS counters under a raised limit would take the 13 and the 32 maps of 8 x 8 to 20.5 and 37.1.
 constexpr int SMALL_MAX_Q = 4;
 constexpr int SMALL_MAX_BINS = 12288;
+constexpr int SMALL_WS_MAX_Q = 2;
 
 struct BinArgs {
     const float* coords;   // [B][2][H*W]
@@ -205,16 +212,22 @@ __global__ __launch_bounds__(256) void bin_scatter_kernel(BinArgs a) {
     }
 }
 
-// Inputs of up to SCAN_T * SMALL_MAX_Q queries and SMALL_MAX_BINS bins: count, scan and scatter in one workgroup, one launch.  Bound by
-// latency: the coordinates' way here, the counters' LDS atomics, the scan and the lists' way out.
+// Count, scan and scatter in one workgroup, one launch, for up to SCAN_T * MAX_Q queries.  Bound by latency: the coordinates' way here, the
+// counters' atomics, the scan and the lists' way out.  LDS: the counters lie in LDS (up to SMALL_MAX_BINS bins) and those of the workspace are
+// neither read nor written; otherwise the workspace's are used, which are zero here and left zero by the scan.
+template <bool LDS>
 __global__ __launch_bounds__(SCAN_T) void bin_small_kernel(BinArgs a) {
-    __shared__ __align__(16) int counts[SMALL_MAX_BINS];
+    constexpr int MAX_Q = LDS ? SMALL_MAX_Q : SMALL_WS_MAX_Q;
+    __shared__ __align__(16) int lds_counts[LDS ? SMALL_MAX_BINS : 1];
+    int* const counts = LDS ? lds_counts : a.ws.bin_count;
+    const int* const offsets = LDS ? lds_counts : a.ws.bin_off;       // where the scan leaves a bin's first position
     const int BN = a.B * a.HW;
-    for (int i = threadIdx.x; i < a.ws.nbins; i += SCAN_T) counts[i] = 0;
-    int bin[SMALL_MAX_Q], rank[SMALL_MAX_Q];
-    float2 xy[SMALL_MAX_Q];
+    if (LDS)
+        for (int i = threadIdx.x; i < a.ws.nbins; i += SCAN_T) counts[i] = 0;
+    int bin[MAX_Q], rank[MAX_Q];
+    float2 xy[MAX_Q];
 #pragma unroll
-    for (int k = 0; k < SMALL_MAX_Q; ++k) {
+    for (int k = 0; k < MAX_Q; ++k) {
         const int q = k * SCAN_T + threadIdx.x;
         bin[k] = -1; rank[k] = 0; xy[k] = make_float2(0.f, 0.f);
         if (q < BN) {
@@ -226,16 +239,16 @@ __global__ __launch_bounds__(SCAN_T) void bin_small_kernel(BinArgs a) {
     }
     __syncthreads();                  // every counter is zero
 #pragma unroll
-    for (int k = 0; k < SMALL_MAX_Q; ++k)
+    for (int k = 0; k < MAX_Q; ++k)
         if (k * SCAN_T < BN) rank[k] = take_rank(counts, bin[k]);      // uniform condition
     __syncthreads();                  // every count is whole
-    scan_cells<SCAN_T, 1, true>(a.ws, counts);
+    scan_cells<SCAN_T, 1, LDS>(a.ws, counts);
     __syncthreads();                  // every offset is there
 #pragma unroll
-    for (int k = 0; k < SMALL_MAX_Q; ++k) {
+    for (int k = 0; k < MAX_Q; ++k) {
         const int q = k * SCAN_T + threadIdx.x;
         if (q < BN && bin[k] >= 0) {
-            const int pos = counts[bin[k]] + rank[k];
+            const int pos = offsets[bin[k]] + rank[k];
             a.ws.perm[pos] = q;
             a.ws.sorted_c[pos] = xy[k];
         }
@@ -320,7 +333,11 @@ hipError_t launch_binning(const corr_pyramid* p, const BinWs& ws, const LookupAr
     a.coords = q.coords; a.B = p->B; a.HW = HW; a.W = p->W; a.L = p->L; a.r = q.r; a.g = p->grid;
     a.ws = ws;
     if (BN <= SCAN_T * SMALL_MAX_Q && ws.nbins <= SMALL_MAX_BINS) {
-        hipLaunchKernelGGL(bin_small_kernel, dim3(1), dim3(SCAN_T), 0, s, a);
+        hipLaunchKernelGGL(bin_small_kernel<true>, dim3(1), dim3(SCAN_T), 0, s, a);
+        return hipGetLastError();
+    }
+    if (BN <= SCAN_T * SMALL_WS_MAX_Q) {
+        hipLaunchKernelGGL(bin_small_kernel<false>, dim3(1), dim3(SCAN_T), 0, s, a);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(bin_count_kernel, dim3((BN + COUNT_T - 1) / COUNT_T), dim3(COUNT_T), 0, s, a);

@@ -2,6 +2,8 @@
 through the library's test hooks: the pooled pyramid levels in each stored representation, against
 the oracle's pyramid, and the plan the binning pass leaves in its workspace (item list and sorted
 query list), against the binning rule written out on the host."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -136,6 +138,37 @@ def test_binning_workspace_against_the_rule(case):
 def test_binning_workspace_at_the_edges_of_the_one_workgroup_path(case):
     """Up to 4096 queries and 12288 bins take one workgroup: 2046, 2145, 4096 and 4097 queries, 12288 and 12544 bins."""
     test_binning_workspace_against_the_rule(case)
+
+
+def _launches(b, call):
+    """Kernels that `call` enqueues: the nodes of a graph captured around it (a first call outside sets up what is set up once)."""
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call()
+    n = ctypes.c_size_t(0)
+    nodes = b.load_library().hipGraphGetNodes           # found in the HIP runtime that the library is linked against
+    nodes.argtypes, nodes.restype = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int
+    assert nodes(g.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("case,want", [((13, 8, 8, 4), 2), ((32, 8, 8, 4), 2), ((16, 8, 16, 4), 2), ((16, 11, 11, 4), 2),
+                                       ((128, 4, 4, 2), 2), ((17, 11, 11, 4), 3), ((1, 14, 32, 4), 2), ((1, 64, 64, 4), 2),
+                                       ((1, 17, 241, 3), 3)])
+def test_launches_of_a_lookup(case, want):
+    """Two launches (binning in one workgroup, block kernel) up to 2048 queries whatever the bins, and up to 4096 where these are at
+    most 12288; three beyond (count, scatter, block kernel).  32 maps of 8 x 8 are 2048 queries and 32768 bins."""
+    B, H, W, L = case
+    b = _binding()
+    dev = torch.device("cuda:0")
+    f1, f2, c = synth.small_case(40 + B, B, H, W, 32, flow_range=4.0)
+    t1, t2, tc = (torch.from_numpy(a).to(dev) for a in (f1, f2, c))
+    pyr = b.corr_pyramid_build(t1, t2, L=L)
+    out = torch.empty((B, L * (2 * R + 1) ** 2, H, W), device=dev)
+    assert _launches(b, lambda: b.corr_sample(t1, pyr, tc, out=out)) == want
+    pyr.destroy()
 
 
 def test_outputs_are_plain_tensors_on_the_current_stream(monkeypatch):
