@@ -9,6 +9,7 @@ import pytest
 
 from oracle import corr_oracle as oracle
 from paper_2505_16942_amd import synth
+from tolerances import FP32_TOL
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -82,21 +83,32 @@ def test_binning_workspace_against_the_rule(case):
     evaluated on the host: every binned query is listed exactly once, in an item of the cell the
     rule gives it; queries the rule leaves out are not listed; items partition the list, hold 1..128
     queries, a cell's items are full except its last; inside a cell queries come by source row mod 8.
-    The first case takes the single-workgroup path (at most 2048 queries), the others the
+    The first case takes the single-workgroup path (at most 4096 queries, counters in LDS), the others the
     count + scatter path."""
-    B, H, W, L, fr = case
+    B, H, W, L, _ = case
     b = _binding()
-    dev = torch.device("cuda:0")
-    f1, f2, c = synth.small_case(700 + H, B, H, W, 32, flow_range=fr)
-    rng = np.random.default_rng(H)
-    out_idx = rng.choice(H * W, size=H * W // 20, replace=False)          # 5 % strays, some far outside the grid
+    f1, f2, c = _strayed_case(700 + H, H, *case)
+    t1, t2, tc = (torch.from_numpy(a).to("cuda:0") for a in (f1, f2, c))
+    pyr = b.corr_pyramid_build(t1, t2, L=L)
+    b.corr_sample(t1, pyr, tc)
+    _check_plan(b, pyr, case, c)
+    pyr.destroy()
+
+
+def _strayed_case(seed, stray_seed, B, H, W, L, fr):
+    """synth.small_case with 5 % strays, some far outside the grid, and coordinates that are not finite or beyond the limit."""
+    f1, f2, c = synth.small_case(seed, B, H, W, 32, flow_range=fr)
+    rng = np.random.default_rng(stray_seed)
+    out_idx = rng.choice(H * W, size=H * W // 20, replace=False)
     c.reshape(B, 2, -1)[0, :, out_idx] = rng.uniform(-400, 400, (out_idx.size, 2)).astype(np.float32)
     c[B - 1, 0, 1, 2] = np.float32("nan")
     c[B - 1, 1, 3, 4] = np.float32("inf")
     c[0, 0, 5, 6] = np.float32(-2e6)
-    t1, t2, tc = (torch.from_numpy(a).to(dev) for a in (f1, f2, c))
-    pyr = b.corr_pyramid_build(t1, t2, L=L)
-    b.corr_sample(t1, pyr, tc)
+    return f1, f2, c
+
+
+def _check_plan(b, pyr, case, c):
+    B, H, W, L, _ = case
     items, perm = b.corr_debug_read_plan(pyr)
     geom0 = b.corr_bin_geometry(H, W, L, 0)
     ok, u, v = _host_rule(c, H, W, L, geom0)
@@ -130,14 +142,33 @@ def test_binning_workspace_against_the_rule(case):
         start += cnt
     st = b.corr_last_block_stats(pyr, 4)
     assert st["items"] == len(items)
+
+
+@pytest.mark.parametrize("case,launches", [((1, 31, 66, 4, 9.0), 2), ((1, 33, 65, 4, 9.0), 2), ((1, 64, 64, 4, 9.0), 2),
+                                           ((1, 17, 241, 3, 9.0), 3), ((48, 9, 9, 2, 3.0), 2), ((49, 9, 9, 2, 3.0), 3),
+                                           ((16, 8, 16, 4, 4.0), 2), ((17, 11, 11, 4, 4.0), 3), ((32, 8, 8, 4, 3.0), 2)])
+def test_binning_workspace_at_the_edges_of_the_one_workgroup_path(case, launches):
+    """One workgroup takes up to 4096 queries and 12288 bins with its counters in LDS, and up to 2048 queries with more bins: 2046, 2145,
+    4096 and 4097 queries, 12288 and 12544 bins; then, of more than 12288 bins, 2048 queries, 2057, and 2048 in 32768 bins.
+    Twice on one workspace, with other coordinates; the second lookup also against the fp32 kernel without binning and on
+    the library's own scratch array."""
+    B, H, W, L, _ = case
+    b = _binding()
+    f1, f2, c = _strayed_case(700 + H, H, *case)
+    c2 = _strayed_case(900 + H, H + 1, *case)[2]
+    t1, t2, tc, tc2 = (torch.from_numpy(a).to("cuda:0") for a in (f1, f2, c, c2))
+    pyr = b.corr_pyramid_build(t1, t2, L=L, reps=b.CORR_REP_SPLIT | b.CORR_REP_F32)
+    out = torch.full((B, L * (2 * R + 1) ** 2, H, W), float("nan"), device="cuda:0")
+    assert _launches(b, lambda: b.corr_sample(t1, pyr, tc, out=out)) == launches
+    for coords, host in ((tc, c), (tc2, c2)):
+        b.corr_sample(t1, pyr, coords, out=out)
+        _check_plan(b, pyr, case, host)
+    want = b.corr_sample(t1, pyr, tc2, mode=b.CORR_MODE_ONDEMAND)
+    err, bound = float((out - want).abs().max()), FP32_TOL * float(want.abs().max())
+    print("max|err| %.3e, bound %.3e" % (err, bound), flush=True)
+    assert err <= bound
+    assert torch.equal(b.corr_sample_static(t1, pyr, tc2), out)
     pyr.destroy()
-
-
-@pytest.mark.parametrize("case", [(1, 31, 66, 4, 9.0), (1, 33, 65, 4, 9.0), (1, 64, 64, 4, 9.0), (1, 17, 241, 3, 9.0),
-                                  (48, 9, 9, 2, 3.0), (49, 9, 9, 2, 3.0)])
-def test_binning_workspace_at_the_edges_of_the_one_workgroup_path(case):
-    """Up to 4096 queries and 12288 bins take one workgroup: 2046, 2145, 4096 and 4097 queries, 12288 and 12544 bins."""
-    test_binning_workspace_against_the_rule(case)
 
 
 def _launches(b, call):
