@@ -17,7 +17,7 @@ LIB_PATH = os.path.join(_PKG, "libcorr_mi355x.so")
 CORR_OK = 0
 CORR_ERR_INVALID_ARG, CORR_ERR_UNSUPPORTED, CORR_ERR_OOM, CORR_ERR_HIP, CORR_ERR_MISSING_REP = -1, -2, -3, -4, -5
 CORR_ERR_TOO_LARGE = -6
-CORR_STATIC_SCRATCH_BYTES = 2 << 20
+CORR_STATIC_SCRATCH_BYTES = 4 << 20
 CORR_MODE_BLOCK, CORR_MODE_ONDEMAND, CORR_MODE_FULLVOLUME = 0, 1, 2
 CORR_PREC_BF16X3, CORR_PREC_BF16 = 0, 1
 CORR_OUT_NCHW, CORR_OUT_NHWC = 0, 1

@@ -40,6 +40,18 @@ def test_header_symbols_are_exported():
     assert sorted(binding.BENCH_EXPORTS) == hooks
 
 
+def test_binding_constants_are_the_headers():
+    """Every CORR_* constant of corr.h that the binding repeats has the header's value."""
+    from paper_2505_16942_amd import binding
+    src = re.sub(r"/\*.*?\*/", "", open(HEADER).read(), flags=re.S)
+    values = {name: int(v) for name, v in re.findall(r"\b(CORR_[A-Z0-9_]+)\s*=\s*(-?\d+)", src)}
+    for name, v, shift in re.findall(r"#define\s+(CORR_[A-Z0-9_]+)\s+\(?(\d+)u?(?:\s*<<\s*(\d+))?\)?", src):
+        values[name] = int(v) << int(shift or 0)
+    shared = {name for name in values if hasattr(binding, name)}
+    assert {"CORR_STATIC_SCRATCH_BYTES", "CORR_ERR_TOO_LARGE", "CORR_REP_BF16", "CORR_OUT_NHWC", "CORR_MODE_BLOCK"} <= shared
+    assert {name: getattr(binding, name) for name in shared} == {name: values[name] for name in shared}
+
+
 def test_full_volume_bytes_matches_closed_form():
     binding, _ = _lib()
     # 4 * B * N * sum_l N_l with floor-halved levels
