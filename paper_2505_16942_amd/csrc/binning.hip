@@ -83,8 +83,8 @@ __device__ __forceinline__ int take_rank(int* bin_count, int bin) {
 
 // One workgroup of T threads: exclusive scan of the bin counts (query offsets) and of the per-cell item
 // counts, CPT consecutive cells per thread and tile of T * CPT cells; writes the item list in cell order and
-// clears the counts for the next lookup.  The counts were produced by device-scope atomics of other
-// workgroups, possibly on other XCDs: a caller that runs in the same kernel as those atomics puts an
+// clears the counts for the next lookup.  Counts that device-scope atomics of other workgroups
+// produced, possibly on other XCDs: a caller that runs in the same kernel as those atomics puts an
 // acquire fence in front (this XCD's L2 may hold stale copies of the lines).
 // LDS: the counts lie in `counts` (LDS) and the offsets go there too; the counts in the workspace are left alone.
 template <int T, int CPT, bool LDS>

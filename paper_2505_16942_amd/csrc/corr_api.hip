@@ -389,7 +389,8 @@ corr_status corr_sample_static(const float* fmap1, const corr_pyramid* pyr, cons
     const BinWs ws = corr_ws_carve(mem, BN, ncells);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // the array keeps the last call's contents, laid out for that call's sizes: the bin counters and
-    // the item / ticket counters must start at zero (fill kernels, so the call can be graph-captured)
+    // the item / ticket counters must start at zero (fill kernels, so the call can be graph-captured).  Binning
+    // in one workgroup needs the bin counters alone, and with its counters in LDS neither; cleared for every input.
     hipError_t e = launch_fill_i32(ws.bin_count, 0, (size_t)ws.nbins, s);
     if (e == hipSuccess) e = launch_fill_i32(ws.n_items, 0, CORR_NCOUNTERS, s);
     LookupArgs q;

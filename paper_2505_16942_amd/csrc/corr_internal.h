@@ -75,7 +75,8 @@ static inline int corr_block_grid(int max_items) {
 
 // Per-lookup planning workspace (device memory).  Sized by corr_ws_layout().
 struct BinWs {
-    int* bin_count;                // [nbins] zero between calls; bin = cell * CORR_SUB + (source row & (CORR_SUB - 1))
+    int* bin_count;                // [nbins] zero between calls; bin = cell * CORR_SUB + (source row & (CORR_SUB - 1)).  Untouched where
+                                   // one workgroup counts in LDS
     int* bin_off;                  // [nbins] exclusive prefix of counts
     int* q_bin;                    // [B*H*W] bin id or -1
     int* q_rank;                   // [B*H*W] slot within the bin
