@@ -10,8 +10,8 @@
 // (max(16 >> l, 1) + 2r + 1) x (max(8 >> l, 1) + 2r + 1) target pixels per
 // level.  A work item is (cell, group of <= 128 of its queries); the blocks of
 // the volume that get computed are exactly the items' window x group products,
-// for every level.  Queries out of range at every level are written as zeros
-// here and never reach the contraction.
+// for every level.  Queries out of range at every level get no bin and never
+// reach the contraction; the block kernel's spare workgroups write their zeros.
 //
 // A counting sort over bins = (cell, source row mod 8), so that a cell's queries
 // come out as runs of x-neighbouring source pixels, row after row: the lanes of
@@ -32,13 +32,14 @@ constexpr int SCAN_CPT = 1;           // cells per thread and tile when its last
                                       // the kernel its two workgroups per CU)
 // The one-workgroup path.  Its counters lie in LDS for up to 4096 queries (SMALL_MAX_Q a thread) and 12288 bins (48 KB, within what a kernel may
 // declare without a raised limit).  Inputs of more bins, batches of many small maps, have them in the workspace and take this path up to 2048 queries
-// (SMALL_WS_MAX_Q a thread).  Whole lookups, D = 256, r = 4, smooth flow, us:
-//   one workgroup with LDS / count and scatter launches: 46 x 62 (2852 queries) 29.4 / 32.0, 40 x 90 30.4 / 32.3, 64 x 64 31.6 / 32.8, 12 maps of
-//   18 x 18 (12288 bins) 45.9 / 47.8; eight queries a thread gain nothing: 2 x 46 x 62 (5704) 42.7 / 41.7, 56 x 128 (7168) 45.3 / 42.8;
+// (SMALL_WS_MAX_Q a thread).  Whole lookups, D = 256, r = 4, smooth flow, us, runs of one form within 0.3 (another seed's flow moves a row by up to 10, both forms alike):
+//   one workgroup with LDS / count and scatter launches: 14 x 32 (448 queries) 24.8 / 29.0, 46 x 62 (2852) 30.2 / 32.9 (31.5 / 35.1 with incoherent flow),
+//   40 x 90 (3600) 31.3 / 32.7, 64 x 64 (4096) 41.3 / 42.5, 12 maps of 18 x 18 (3888 queries, 12288 bins) 48.1 / 50.3; eight queries a thread lose:
+//   2 x 46 x 62 (5704) 43.8 / 42.7, 56 x 128 (7168) 46.7 / 43.7;
 //   one workgroup with LDS / with the workspace: 12 maps of 8 x 8 (768 queries, 12288 bins) 20.2 / 21.5;
-//   one workgroup with the workspace / count and scatter launches: 13 maps of 8 x 8 (13312 bins) 21.8 / 25.7, 32 (2048 queries, 32768 bins) 41.5 / 44.0;
-//   four queries a thread: 13 maps of 17 x 17 (3757 queries) 48.2 / 47.5, 20 of 14 x 14 (3920) 52.3 / 51.8.
-// Open: LDS counters under a raised limit would take the 13 and the 32 maps of 8 x 8 to 20.5 and 37.1.
+//   one workgroup with the workspace / count and scatter launches: 13 maps of 8 x 8 (13312 bins) 22.2 / 26.1, 32 (2048 queries, 32768 bins) 42.4 / 44.9,
+//   16 of 11 x 11 (1936 queries) 43.4 / 46.2; with four queries a thread no gain: 13 maps of 17 x 17 (3757) 49.3 / 49.3, 20 of 14 x 14 (3920) 52.3 / 51.6.
+// Open: LDS counters under a raised limit would take the 13 and the 32 maps of 8 x 8 to 20.8 and 38.7, the 16 of 11 x 11 to 41.4.
 constexpr int SMALL_MAX_Q = 4;
 constexpr int SMALL_MAX_BINS = 12288;
 constexpr int SMALL_WS_MAX_Q = 2;

@@ -83,8 +83,8 @@ def test_binning_workspace_against_the_rule(case):
     evaluated on the host: every binned query is listed exactly once, in an item of the cell the
     rule gives it; queries the rule leaves out are not listed; items partition the list, hold 1..128
     queries, a cell's items are full except its last; inside a cell queries come by source row mod 8.
-    The first case takes the single-workgroup path (at most 4096 queries, counters in LDS), the others the
-    count + scatter path."""
+    The first case takes the single-workgroup path (up to 4096 queries and 12288 bins, or up to 2048 queries), the
+    others the count + scatter path."""
     B, H, W, L, _ = case
     b = _binding()
     f1, f2, c = _strayed_case(700 + H, H, *case)
